@@ -66,28 +66,45 @@ struct StageArgs {
   const int4* stab;
 };
 
-constexpr int SS = 16;       // sub-tile edge of the in-tile sweep
-constexpr int TP = TB + 2;   // LDS row stride of the tile arrays (doubles)
+// A work group of a stage launch: eight waves, two per SIMD.
+constexpr int ST = 512;
 
-// LDS of a sweeping workgroup. Ls, Us: the diagonal factor blocks L_II and
-// U_JJ with zero columns 64, 65 (Ls) and zero rows 64, 65 (Us) for source
-// blocks that do not exist. Et, Ct: the tile's E and C as its sub-tiles finish (the
-// operands of the in-tile feedback products); before the sweep the same bytes
-// stage the two neighbour products.
+// The sweep of one tile: 16 x 16 blocks of 4 x 4 entries in four bands.
+constexpr int BS = 4;              // block edge
+constexpr int NB = TB / BS;        // blocks per tile edge
+constexpr int BANDS = ST / 128;    // bands, each with a pair of waves
+constexpr int BANDB = NB / BANDS;  // block rows of a band
+constexpr int STEPS = NB + BANDB - 1;
+constexpr int PAD = BS * (BANDB - 1);
+constexpr int TE = TB + PAD;       // LDS row stride of the tile arrays (doubles)
+constexpr int TEN = TB * TE + PAD;
+constexpr int TX = TB + 4 * BS;    // of Et and Xs: rows of four blocks of 32 lanes hit 64 different banks
+constexpr int TXN = TB * TX + 4 * BS;
+
+// LDS of a sweeping work group. A row of the arrays starts with 12 columns of
+// zeros (the row before ends in them): a bank whose block column is still to
+// come or already past the tile's edge reads and writes zeros there.
+//   Xs: X plus the right feedback so far, then the corrected values
+//   Ct: the down feedback so far, then C = L E
+//   Et: the errors, as the blocks finish
+//   Us: U_JJ, unit upper. Block row J' is read up to block column J' + 15: past
+//     a row's end follow its 12 zeros and the lower triangle of the next rows.
+//     What is read in front of Us (Ct) or behind it (Et) belongs to blocks
+//     outside the tile and meets a zero; like everything here it is finite.
+// Before the sweep the bytes of Et and Xs stage the two neighbour products.
 struct SweepSmem {
-  double Ls[TB][TP];
-  double Us[TB + 2][TP];
+  double Ct[TEN];
+  double Us[TB * TE];
   union {
     struct {
-      double Et[TB][TP];
-      double Ct[TB][TP];
-    } t;
+      double Et[TXN];
+      double Xs[TXN];
+    };
     Stage64 g;
-    double T[TB][TB + 1];
-  } x;
-  double scr[4][SS][SS + 1]; // per wave: MFMA-layout to block-layout transfer
-  double red[NT / 64];
-  int done[4];               // per wave: sub-tiles finished (release/acquire, workgroup scope)
+  };
+  double red[ST / 64];
+  int done[BANDS];  // per band: steps finished
+  int prep[BANDS];  // per band: steps whose values in Xs and Ct are ready
 };
 
 // Staging of one 32-deep chunk of a delivery product, filled by direct
@@ -164,23 +181,23 @@ __device__ __forceinline__ TaskOp task_op(const StageArgs& a, int4 tk) {
 typedef __attribute__((address_space(3))) void lds_void;
 
 // Chunk c of task T into d (source tile c / 2, its columns (rows of B)
-// 32 (c % 2) ..): wave w moves the left-operand row blocks j = w + 4i (rows
-// 4j .. 4j+3, i < 4 nr: 1 KB of contiguous memory in S order) and the
-// right-operand rows k = w + 4i (i < 8), each a 1 KB direct global -> LDS
+// 32 (c % 2) ..): wave w moves the left-operand row blocks j = w + 8i (rows
+// 4j .. 4j+3, i < 2 nr: 1 KB of contiguous memory in S order) and the
+// right-operand rows k = w + 8i (i < 4), each a 1 KB direct global -> LDS
 // load. Lane l of a left-operand load takes the 16-byte piece
 // (l & 15) ^ (l >> 4) of row 4j + (l >> 4); of a right-operand load the
 // columns 2l, 2l+1 (clamped to the target: never used past it).
 // (i0, i1 select the part i0 <= i < i1 of the loads)
 __device__ __forceinline__ void task_issue(const TaskOp& T, int c, TaskChunk& d, int w, int l, int i0 = 0,
-                                           int i1 = 8) {
+                                           int i1 = 4) {
   const int ar = l >> 4, ap = (l & 15) ^ ar;
   const double* ac = T.A + (int64_t)(c >> 1) * 4096 + (c & 1) * 2048;
   const int col = min(2 * l, TB * T.nc - 2);
   const double* pb = T.B + (int64_t)(c >> 1) * T.bks + (c & 1) * 32 * TB + (col >> 6) * 4096 + (col & 63);
 #pragma unroll
   for (int i = i0; i < i1; ++i) {
-    const int j = w + 4 * i;
-    if (i < 4 * T.nr) {
+    const int j = w + 8 * i;
+    if (i < 2 * T.nr) {
       const double* pa = ac + (j >> 4) * T.ars + (4 * (j & 15) + ar) * 32 + 2 * ap;
       __builtin_amdgcn_global_load_lds((const void*)pa, (lds_void*)&d.a[j][0], 16, 0, 0);
     }
@@ -190,15 +207,14 @@ __device__ __forceinline__ void task_issue(const TaskOp& T, int c, TaskChunk& d,
 
 // The part of a (64 nr) x (64 nc) target that wave w computes, as NI x NJ
 // MFMA blocks of 16 x 16 from row rb and column cb:
-//   2 x 2 tiles: 64 x 64 quadrant (w >> 1, w & 1)      NI = NJ = 4
-//   2 x 1 tiles: rows 32 w .. 32 w + 31, all 64 columns NI = 2, NJ = 4
-//   1 x 2 tiles: all 64 rows, columns 32 w .. 32 w + 31 NI = 4, NJ = 2
-//   1 x 1 tile : 32 x 32 quadrant (w >> 1, w & 1)      NI = NJ = 2
+//   2 x 2 tiles: 64 x 32  NI = 4, NJ = 2
+//   2 x 1 and 1 x 2 tiles: 32 x 32  NI = NJ = 2
+//   1 x 1 tile : 32 x 16  NI = 2, NJ = 1
 __device__ __forceinline__ void task_part(const TaskOp& T, int w, int& rb, int& cb) {
-  if (T.nr == 2 && T.nc == 2) { rb = 64 * (w >> 1); cb = 64 * (w & 1); }
-  else if (T.nr == 2) { rb = 32 * w; cb = 0; }
-  else if (T.nc == 2) { rb = 0; cb = 32 * w; }
-  else { rb = 32 * (w >> 1); cb = 32 * (w & 1); }
+  if (T.nr == 2 && T.nc == 2) { rb = 64 * (w >> 2); cb = 32 * (w & 3); }
+  else if (T.nr == 2) { rb = 32 * (w >> 1); cb = 32 * (w & 1); }
+  else if (T.nc == 2) { rb = 32 * (w >> 2); cb = 32 * (w & 3); }
+  else { rb = 32 * (w >> 2); cb = 16 * (w & 3); }
 }
 
 // Accumulators of the wave's part: the old target values (a delivery that
@@ -210,7 +226,7 @@ __device__ __forceinline__ int64_t task_at(const TaskOp& T, int row, int col) {
 }
 
 template <int NI, int NJ>
-__device__ __forceinline__ void task_init(d4 (&acc)[4][4], const TaskOp& T, int rb, int cb, int l) {
+__device__ __forceinline__ void task_init(d4 (&acc)[NI][NJ], const TaskOp& T, int rb, int cb, int l) {
   if (!T.ow) {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
@@ -231,7 +247,7 @@ __device__ __forceinline__ void task_init(d4 (&acc)[4][4], const TaskOp& T, int 
 }
 
 template <int NI, int NJ>
-__device__ __forceinline__ void task_store(const d4 (&acc)[4][4], const TaskOp& T, int rb, int cb,
+__device__ __forceinline__ void task_store(const d4 (&acc)[NI][NJ], const TaskOp& T, int rb, int cb,
                                            int l) {
 #pragma unroll
   for (int i = 0; i < NI; ++i)
@@ -247,7 +263,7 @@ __device__ __forceinline__ void task_store(const d4 (&acc)[4][4], const TaskOp& 
 // sets), the reads spread between the MFMAs; mid() runs half-way (before the
 // MFMAs of k-step KQ / 8).
 template <int NI, int NJ, typename Mid>
-__device__ __forceinline__ void task_mma(d4 (&acc)[4][4], const TaskChunk& st, int rb, int cb, int l,
+__device__ __forceinline__ void task_mma(d4 (&acc)[NI][NJ], const TaskChunk& st, int rb, int cb, int l,
                                          Mid&& mid) {
   const int r0 = l & 15, rr = r0 & 3;
   double av[2][NI], bv[2][NJ];
@@ -297,7 +313,7 @@ __device__ __forceinline__ void task_mma(d4 (&acc)[4][4], const TaskChunk& st, i
 template <int NI, int NJ>
 __device__ void run_stream(const StageArgs& a, const int4* tk, int n, TaskSmem& sm) {
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
-  d4 acc[4][4];
+  d4 acc[NI][NJ];
   TaskOp T = task_op(a, tk[0]);
   int rb, cb;
   task_part(T, w, rb, cb);
@@ -309,15 +325,15 @@ __device__ void run_stream(const StageArgs& a, const int4* tk, int n, TaskSmem& 
     // the next chunk's loads go out in two halves, the second one half-way
     // through this chunk's MFMAs (one batch of them stalls this wave's issue
     // until the memory pipeline takes it)
-    if (!last) task_issue(T, c + 1, sm.buf[p ^ 1], w, l, 0, 4);
-    // chunk c has landed (issued after it: the first half of the next, 8 loads)
-    if (!last) __builtin_amdgcn_s_waitcnt(0x0f78);  // vmcnt(8)
+    if (!last) task_issue(T, c + 1, sm.buf[p ^ 1], w, l, 0, 2);
+    // chunk c has landed (issued after it: the first half of the next, 4 loads)
+    if (!last) __builtin_amdgcn_s_waitcnt(0x0f74);  // vmcnt(4)
     else __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
     // a bare barrier: the wait above already covers this wave's part of
     // chunk c, and a fenced barrier would also wait for the next chunk
     asm volatile("s_barrier" ::: "memory");
     task_mma<NI, NJ>(acc, sm.buf[p], rb, cb, l, [&]() {
-      if (!last) task_issue(T, c + 1, sm.buf[p ^ 1], w, l, 4, 8);
+      if (!last) task_issue(T, c + 1, sm.buf[p ^ 1], w, l, 2, 4);
     });
     // buffer p is refilled next: every wave's reads of it are complete
     // before the barrier, while the next chunk stays in flight
@@ -343,481 +359,494 @@ __device__ void run_bin(const StageArgs& a, int4 bin, TaskSmem& sm) {
   const int4* tk = a.tasks + bin.x;
   const int n4 = bin.y & 0xffff, n21 = bin.y >> 16, n12 = bin.z & 0xffff, n11 = bin.z >> 16;
   bool busy = false;  // a group before this one used the staging buffers
-  if (n4) { run_stream<4, 4>(a, tk, n4, sm); busy = true; }
+  if (n4) { run_stream<4, 2>(a, tk, n4, sm); busy = true; }
   tk += n4;
-  if (n21) { if (busy) __syncthreads(); run_stream<2, 4>(a, tk, n21, sm); busy = true; }
+  if (n21) { if (busy) __syncthreads(); run_stream<2, 2>(a, tk, n21, sm); busy = true; }
   tk += n21;
-  if (n12) { if (busy) __syncthreads(); run_stream<4, 2>(a, tk, n12, sm); busy = true; }
+  if (n12) { if (busy) __syncthreads(); run_stream<2, 2>(a, tk, n12, sm); busy = true; }
   tk += n12;
-  if (n11) { if (busy) __syncthreads(); run_stream<2, 2>(a, tk, n11, sm); }
+  if (n11) { if (busy) __syncthreads(); run_stream<2, 1>(a, tk, n11, sm); }
 }
 
-// acc += A (16 x K) B (K x 16) on MFMA, both operands row-major in LDS with
-// row strides lda, ldb; K a compile-time multiple of 4: every operand load is
-// issued first.
-template <int K>
-__device__ __forceinline__ void mma16k(d4& acc, const double* pa, int lda, const double* pb, int ldb) {
-  if constexpr (K > 0) {
-    const int l = threadIdx.x & 63;
-    const double* qa = pa + (l & 15) * lda + (l >> 4);
-    const double* qb = pb + (l >> 4) * ldb + (l & 15);
-    double av[K / 4], bv[K / 4];
-#pragma unroll
-    for (int s = 0; s < K / 4; ++s) {
-      av[s] = qa[4 * s];
-      bv[s] = qb[4 * s * ldb];
-    }
-#pragma unroll
-    for (int s = 0; s < K / 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s], bv[s], acc, 0, 0, 0);
-  }
+typedef __attribute__((address_space(3))) double lds_double;
+
+// v_mfma_f64_4x4x4: four independent 4 x 4 products, one per bank of four
+// lanes in every row of 16. With lane = 16 r + 4 b + c, bank b:
+//   A lane holds A[c][r], B lane B[r][c], D lane D[r][c].
+// So a value in D's layout is the transpose of what it is as operand A, and
+// itself as operand B.
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
-// Per-lane constants of a band sweep.
-struct Band {
-  int w, l, p, q, br, gi0, gj0;
-  double* Et;      // the tile's E (R order) and C (S order)
-  double* Ct;
-  double l10;      // L[br+1][br]
-  double u01[4];   // U[uc+2q][uc+2q+1] of sub-tile c (uc = 16 c)
-  double dl[2];    // 1 / lamL of the lane's two rows
-  bool interior;   // the whole tile lies inside the matrix
-  int32_t* zr[2];  // Z and Y at the lane's two rows, column 2q of the tile
-  void* yr[2];
-};
-
-// Bounded wait until a band's release counter reaches v (workgroup-scope
-// acquire); a wait that runs out raises the time-out flag instead of hanging.
-__device__ __forceinline__ void wait_band(const int* done, int v, int& bad) {
+// Bounded wait until a band's counter reaches v; a wait that runs out raises
+// the time-out flag instead of hanging. A counter is written after the values
+// it stands for by the same wave, and LDS serves a wave in order.
+__device__ __forceinline__ int load_count(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// seen: the last value read; the counter is read again only if that is short
+__device__ __forceinline__ void wait_count(const int* p, int v, int& seen, int& bad) {
   int spins = 0;
-  while (__hip_atomic_load(done, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < v) {
-    __builtin_amdgcn_s_sleep(1);
+  while (__builtin_amdgcn_readfirstlane(seen) < v) {
+    seen = load_count(p);
     if (++spins > (1 << 22)) {
       bad |= FLAG_TIMEOUT;
       break;
     }
   }
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void store_count(int* p, int v) {
+  asm volatile("" ::: "memory");
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// acc += A (16 x K) B (K x 16) on MFMA for a K that is a multiple of 16 known
-// only at run time (the wave's band index); operands row-major in LDS.
-__device__ __forceinline__ void mma16(d4& acc, const double* pa, int lda, const double* pb, int ldb, int K) {
-  const int l = threadIdx.x & 63;
-  const double* qa = pa + (l & 15) * lda + (l >> 4);
-  const double* qb = pb + (l >> 4) * ldb + (l & 15);
+// y += w * (e of lane N of the lane's row of 16), a DPP broadcast inside the
+// multiply-add.
+#define G2D_PUSH(N_, y_, e_, w_) \
+  "v_fmac_f64_dpp %[" #y_ "], %[" #e_ "], %[" #w_ "] row_newbcast:" #N_ " row_mask:0xf bank_mask:0xf\n\t"
+// e = rint(y) - y. A DPP operand may be read two wait states after it was
+// written: two of the next weights are formed in between.
+#define G2D_ERR(e_, y_) "v_rndne_f64 %[" #e_ "], %[" #y_ "]\n\tv_add_f64 %[" #e_ "], %[" #e_ "], -%[" #y_ "]\n\t"
+#define G2D_WEIGHT(w_, l_, u_, s_) "v_fma_f64 %[" #w_ "], %[" #l_ "], %[" #u_ "], %[" #s_ "]\n\t"
+
+// The seven entry anti-diagonals of a 4 x 4 block, a lane per entry (i, j) = (lane / 4 % 4,
+// lane % 4): on entry y holds everything from outside the block, on return the
+// corrected values; e the errors. Entry n = 4 i' + j' reaches the others with the
+// weight L[i][i'] U[j'][j] (self[n] takes the 1 at the entry itself away). One
+// block of assembly, so that each weight stands where the chain has to wait.
+__device__ __forceinline__ void block_chain(double& y, double& e, const double (&l)[BS], const double (&u)[BS],
+                                            const double (&self)[15]) {
+  double w0 = fma(l[0], u[0], self[0]), w1, w2, w3, w4, w5, w6;
+  asm volatile(
+      G2D_ERR(e, y) G2D_WEIGHT(w1, l0, u1, s1) G2D_WEIGHT(w2, l1, u0, s4)
+      G2D_PUSH(0, y, e, w0)
+      G2D_ERR(e, y) G2D_WEIGHT(w3, l0, u2, s2) G2D_WEIGHT(w4, l1, u1, s5)
+      G2D_PUSH(1, y, e, w1) G2D_WEIGHT(w5, l2, u0, s8) G2D_PUSH(4, y, e, w2)
+      G2D_ERR(e, y) G2D_WEIGHT(w0, l0, u3, s3) G2D_WEIGHT(w1, l1, u2, s6)
+      G2D_PUSH(2, y, e, w3) G2D_WEIGHT(w2, l2, u1, s9) G2D_PUSH(5, y, e, w4) G2D_WEIGHT(w6, l3, u0, s12)
+      G2D_PUSH(8, y, e, w5)
+      G2D_ERR(e, y) G2D_WEIGHT(w3, l1, u3, s7) G2D_WEIGHT(w4, l2, u2, s10)
+      G2D_PUSH(3, y, e, w0) G2D_WEIGHT(w5, l3, u1, s13) G2D_PUSH(6, y, e, w1)
+      G2D_PUSH(9, y, e, w2) G2D_PUSH(12, y, e, w6)
+      G2D_ERR(e, y) G2D_WEIGHT(w0, l2, u3, s11) G2D_WEIGHT(w1, l3, u2, s14)
+      G2D_PUSH(7, y, e, w3) G2D_PUSH(10, y, e, w4) G2D_PUSH(13, y, e, w5)
+      G2D_ERR(e, y) "s_nop 1\n\t"
+      G2D_PUSH(11, y, e, w0) G2D_PUSH(14, y, e, w1)
+      G2D_ERR(e, y)
+      : [y] "+&v"(y), [e] "=&v"(e), [w0] "+&v"(w0), [w1] "=&v"(w1), [w2] "=&v"(w2), [w3] "=&v"(w3),
+        [w4] "=&v"(w4), [w5] "=&v"(w5), [w6] "=&v"(w6)
+      : [l0] "v"(l[0]), [l1] "v"(l[1]), [l2] "v"(l[2]), [l3] "v"(l[3]), [u0] "v"(u[0]), [u1] "v"(u[1]),
+        [u2] "v"(u[2]), [u3] "v"(u[3]), [s1] "v"(self[1]), [s2] "v"(self[2]), [s3] "v"(self[3]),
+        [s4] "v"(self[4]), [s5] "v"(self[5]), [s6] "v"(self[6]), [s7] "v"(self[7]), [s8] "v"(self[8]),
+        [s9] "v"(self[9]), [s10] "v"(self[10]), [s11] "v"(self[11]), [s12] "v"(self[12]), [s13] "v"(self[13]),
+        [s14] "v"(self[14]));
+}
+
+// What bounds a tile sweep is the chain of entry anti-diagonals, one after
+// another: with all 64 lanes rounding 2 x 2 blocks of a 16 x 16 sub-tile in each
+// of 15 steps it took about 8.9k cycles a sub-tile and 62k a tile (26 us; every
+// step waited for an LDS exchange of errors and C and issued 49 instructions).
+// Blocks of 4 x 4 in rows of 16 lanes exchange errors by DPP broadcasts and
+// everything between blocks goes through the matrix unit: 232 cycles for a
+// block's seven anti-diagonals, about 800 for a whole step of a wave that runs
+// by itself. fp64 vector and matrix instructions share one pipe, so a band's
+// older feedback, prepared on another SIMD, still delays the chains there. Whole
+// problems went from 182 to 130 us (200 x 120), from 829 to 696 us (512 x 384,
+// factorisation included), 4096 x 4096 rounds in 5.8 instead of 6.25 ms.
+// Algorithm 3 on the 16 rows of band W. In step s, row-of-16 g of the wave
+// rounds the 4 x 4 block (g, J = s - g) of the band, a lane per entry (lane =
+// 16 g + 4 i + j), so the wave moves over the band along its block
+// anti-diagonals in 19 steps. A step has two parts:
+//   - the block's seven entry anti-diagonals. Each finished entry's error
+//     reaches every later entry of its block as one multiply-add with a
+//     broadcast operand: L[i][i'] U[j'][j] e, the weights formed beforehand.
+//   - what the next step waits for, with matrix instructions: C = L E + D of
+//     the block just finished (kept transposed: operand A as it is), its right
+//     feedback C U on the next block, and the down feedback of the band's block
+//     above the next one (as D U, and added to D). The two layouts meet in LDS.
+// The feedback of the step before it is added on the way; all older feedback
+// is prepared by the band's second wave (prepare_band) three steps ahead. A bank whose block column is before the tile's first or past
+// the last holds zeros throughout.
+template <int W>
+__device__ __forceinline__ void sweep_band(const double* Ltile, SweepSmem& sm, int l, int& bad) {
+  const int r = l >> 4, b = (l >> 2) & 3, c = l & 3;  // matrix layout: bank b, entry (r, c)
+  // L[.][.] of the lane's block row against its own block and the two above
+  const int lr = BS * (BANDB * W + b) + c;
+  const double v0 = Ltile[s_idx(lr, BS * (BANDB * W + b) + r)];
+  const double v1 = Ltile[s_idx(lr, BS * (BANDB * W + max(b - 1, 0)) + r)];
+  const double v2 = Ltile[s_idx(lr, BS * (BANDB * W + max(b - 2, 0)) + r)];
+  // chain layout: block row r, entry (b, c)
+  const int cr = BS * (BANDB * W + r);
+  double lw[BS], self[15];
+#pragma unroll
+  for (int k = 0; k < BS; ++k) lw[k] = Ltile[s_idx(cr + b, cr + k)];
+  const double la0 = r < c ? v0 : r == c ? 1.0 : 0.0, la1 = b > 0 ? v1 : 0.0, la2 = b > 1 ? v2 : 0.0;
+#pragma unroll
+  for (int k = 0; k < BS; ++k) lw[k] = k < b ? lw[k] : k == b ? 1.0 : 0.0;
+#pragma unroll
+  for (int k = 0; k < 15; ++k) self[k] = (l & 15) == k ? -1.0 : 0.0;
+
+  // LDS addresses of step 0; one block column further per step
+  const int mrow = BS * (BANDB * W + b);
+  lds_double* pu = (lds_double*)(sm.Us + (r - BS * b) * TE + c - BS * b);  // block (J, J) of U
+  lds_double* pw = (lds_double*)(sm.Us - BS * r * TE + c - BS * r);        // the same, chain layout
+  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TE + r - BS * b);  // Ct, transposed
+  // Et, matrix layout, two block rows up (their weights are zero where the
+  // band has none); Xs is at a constant distance
+  lds_double* pe = (lds_double*)(sm.Et + PAD + (mrow - 2 * BS + r) * TX + c - BS * b);
+  lds_double* po = (lds_double*)(sm.Et + PAD + (cr + b) * TX + c - BS * r);    // Et, chain layout
+  constexpr int EX = TXN;  // from Et to Xs
+
+  int seen = 0;
+  wait_count(&sm.prep[W], 1, seen, bad);
+  double dt = pt[0], ct = 0.0, u2 = 0.0;
+  pe[EX + 2 * BS * TX] = mfma4(dt, pu[0], pe[EX + 2 * BS * TX]);
+  asm volatile("" ::: "memory");
+  double y = po[EX], err;
 #pragma unroll 1
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    double av[4], bv[4];
+  for (int s = 0; s < STEPS; ++s) {
+    // (opaque addresses: constant offsets from them fit the LDS instructions)
+    asm volatile("" : "+v"(pu), "+v"(pw), "+v"(pt), "+v"(pe), "+v"(po));
+    // operands of the next step, read while this one's chain runs; if its
+    // values were not ready yet they are read again behind it
+    double uw[BS];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      av[s] = qa[k0 + 4 * s];
-      bv[s] = qb[(k0 + 4 * s) * ldb];
+    for (int k = 0; k < BS; ++k) uw[k] = pw[k * TE];
+    seen = load_count(&sm.prep[W]);
+    asm volatile("" ::: "memory");
+    double xn = pe[EX + 2 * BS * TX + BS], dn = pt[BS];
+    const double e2 = pe[BS], u1 = pu[BS], un = pu[BS * TE + BS], u2n = pu[2 * BS];
+    block_chain(y, err, lw, uw, self);
+    po[0] = err;
+    po[EX] = y;
+    asm volatile("" ::: "memory");
+    const double em = pe[2 * BS * TX], e1 = pe[BS * TX + BS];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) < min(s + 2, STEPS), 0)) {
+      wait_count(&sm.prep[W], min(s + 2, STEPS), seen, bad);
+      xn = pe[EX + 2 * BS * TX + BS];
+      dn = pt[BS];
     }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s], bv[s], acc, 0, 0, 0);
+    xn = mfma4(ct, u2, xn);
+    dn = mfma4(e2, la2, dn);
+    ct = mfma4(em, la0, dt);
+    dt = mfma4(e1, la1, dn);
+    double ym = mfma4(ct, u1, xn);
+    ym = mfma4(dt, un, ym);
+    pt[0] = ct;
+    pe[EX + 2 * BS * TX + BS] = ym;
+    asm volatile("" ::: "memory");
+    y = po[EX + BS];
+    store_count(&sm.done[W], s + 1);
+    u2 = u2n;
+    pu += BS * TE + BS;
+    pw += BS * TE + BS;
+    pt += BS;
+    pe += BS;
+    po += BS;
   }
 }
 
-// Sub-tile (w, C) of the band: wait for the band above, add the in-tile
-// feedback of the finished sub-tiles above and to the left, run Algorithm 3
-// on the 16 x 16 block, publish E and C, write the outputs.
-template <typename T, int C>
-__device__ __forceinline__ void sub_tile(const StageArgs& a, SweepSmem& sm, const Band& b,
-                                         double (&Dc)[2][2], double (&Rc)[2][2], const double (&dc)[2],
-                                         double& part, int& bad) {
-  const int w = b.w, l = b.l, p = b.p, q = b.q, br = b.br;
-  constexpr int uc = SS * C;
-  // the band above must have finished sub-tile C
-  if (w > 0) wait_band(&sm.done[w - 1], C + 1, bad);
-  // feedback from the finished sub-tiles above (same column) and to the left
-  // (same band) inside this tile
-  {
-    d4 aD = {0.0, 0.0, 0.0, 0.0}, aR = {0.0, 0.0, 0.0, 0.0};
-    mma16k<SS * C>(aR, &sm.x.t.Ct[SS * w][0], TP, &sm.Us[0][uc], TP);
-    mma16(aD, &sm.Ls[SS * w][0], TP, &sm.x.t.Et[0][uc], TP, SS * w);
-    double(*sc)[SS + 1] = sm.scr[w];
+// The second wave of band W: three steps ahead of the first it completes the
+// values that step k starts from. acc[d] holds the right feedback that the
+// blocks finished so far (steps <= k - 3) have on the blocks of step k + d; the
+// down feedback comes from the band's block three above and from all blocks of
+// the bands above.
+template <int W>
+__device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm, int l, int& bad) {
+  const int r = l >> 4, b = (l >> 2) & 3, c = l & 3;
+  const int mrow = BS * (BANDB * W + b), lr = mrow + c;
+  constexpr int NQ = BANDB * W;           // blocks above the band
+  constexpr int NO = W > 1 ? NQ - BANDB : 0;  // of which not in the band next above
+  double lb[NQ > 0 ? NQ : 1];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sc[4 * r + (l >> 4)][l & 15] = aD[r];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) Dc[i][j] += sc[2 * p + i][2 * q + j];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sc[4 * r + (l >> 4)][l & 15] = aR[r];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) Rc[i][j] += sc[2 * p + i][2 * q + j];
-    __builtin_amdgcn_wave_barrier();
-  }
+  for (int q = 0; q < NQ; ++q) lb[q] = Ltile[s_idx(lr, BS * q + r)];
+  const double v3 = Ltile[s_idx(lr, max(mrow - 3 * BS, 0) + r)];
+  const double la3 = b > 2 ? v3 : 0.0;
 
-  // Algorithm 3 on the 16 x 16 sub-tile, one 2 x 2 block per lane. The
-  // blocks form an 8 x 8 grid swept along its anti-diagonals: block (p, q)
-  // is rounded in step p + q (an in-block chain of three entry
-  // anti-diagonals). In every step each lane first adds the feedback of the
-  // blocks finished in the step before that lie above it in its block column
-  // (errors through L, Alg. 3 push down) or left of it in its block row (C
-  // through U, push right). Those source blocks are read unconditionally
-  // (every LDS word they can reach holds a finite value); a source that does
-  // not feed the lane gets a zero weight: the zero column of Ls, the zero rows
-  // of Us, or, for the block on the lane's own diagonal, the 2 x 2 diagonal
-  // blocks of Ls and Us, which hold zeros during the sweep (their one
-  // off-diagonal entry is kept in a register).
-  // So a lane's accumulators stop changing after its own step, and every
-  // lane runs the rounding chain in every step without a branch: before its
-  // step it publishes finite placeholders that nobody reads with a nonzero
-  // weight, from its step on the final E and C of its block (read back by
-  // the same wave in the next step: LDS is in order within a wave, no
-  // barrier). The results of the last step are every lane's final values.
-  const double u01 = b.u01[C];
-  const double l10 = b.l10;
-  const double ul = u01 * l10;
-  double* const eown = &sm.x.t.Et[br][uc + 2 * q];
-  double* const cown = &sm.x.t.Ct[br][uc + 2 * q];
-  // sources at step k: E rows 16 w + 2 (k-1-q) .. +1 at the lane's columns,
-  // C columns uc + 2 (k-1-p) .. +1 at the lane's rows (a per-lane base plus
-  // a constant offset: no address arithmetic in the steps)
-  const double* const pe0 = &sm.x.t.Et[0][0] + (SS * w - 2 - 2 * q) * TP + uc + 2 * q;
-  const double* const pc0 = &sm.x.t.Ct[0][0] + br * TP + uc - 2 - 2 * p;
-  // weights of step k: L rows br, br+1 at columns SS w - 2 - 2 q + 2 k, and U
-  // rows uc - 2 - 2 p + 2 k, +1 at columns uc + 2q, +1; a source that does not
-  // feed the lane reads zeros at the same step offset instead: the zero rows
-  // 64, 65 of Us for L (the offset runs along columns) and the zero columns
-  // 64, 65 of Ls for U (it runs along rows). So a step selects one of two
-  // bases per operand and adds a constant.
-  const double* const plv = &sm.Ls[br][0] + SS * w - 2 - 2 * q;
-  const double* const plz = &sm.Us[TB][0];
-  const double* const puv = &sm.Us[0][0] + (uc - 2 - 2 * p) * TP + uc + 2 * q;
-  const double* const puz = &sm.Ls[0][TB];
-  // the weights of step k do not depend on the sweep: they are read one step
-  // ahead, after that step's sources, so that the wait for the sources (the
-  // errors and C just written by the step before) covers four reads only
-  double2 wl[2][2], wu[2][2];
-  auto weights = [&](int k, double2(&l)[2], double2(&u)[2]) {
-    const bool vr = (unsigned)(k - 1 - q) < (unsigned)p;  // source block row k-1-q above
-    const bool vc = (unsigned)(k - 1 - p) < (unsigned)q;  // source block column k-1-p left
-    const double* pl = (vr ? plv : plz) + 2 * k;
-    const double* pu = (vc ? puv : puz) + 2 * k * TP;
-    l[0] = *reinterpret_cast<const double2*>(pl);
-    l[1] = *reinterpret_cast<const double2*>(pl + TP);
-    u[0] = *reinterpret_cast<const double2*>(pu);
-    u[1] = *reinterpret_cast<const double2*>(pu + TP);
+  // LDS addresses of step 0
+  lds_double* pu = (lds_double*)(sm.Us + (r - BS * b - 3 * BS) * TE + c - BS * b);  // block (J - 3, J) of U
+  lds_double* pm = (lds_double*)(sm.Xs + PAD + (mrow + r) * TX + c - BS * b);
+  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TE + r - BS * b);
+  lds_double* pe = (lds_double*)(sm.Et + PAD + r * TX + c - BS * b);
+  lds_double* p3 = (lds_double*)(sm.Et + PAD + (mrow - 3 * BS + r) * TX + c - BS * b);
+
+  constexpr int ND = NB - 3;
+  double acc[ND + 1], uv[ND], ev[NQ > 0 ? NQ : 1];
+#pragma unroll
+  for (int d = 0; d <= ND; ++d) acc[d] = 0.0;
+  int seen = 0, above = 0;  // steps known to be finished: this band, the band above
+  int* const up = &sm.done[W > 0 ? W - 1 : 0];
+  if (W > 0) wait_count(up, BANDB, above, bad);
+  // A step's values, but for its right feedback, from the down feedback of the
+  // bands above; those of the blocks further above are there (the band next
+  // above waited for them before its own last steps).
+  double x, d0, d1;
+  auto begin = [&](int at) {
+    x = pm[at];
+    d0 = pt[at];
+    d1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NO; ++q) ev[q] = pe[BS * q * TX + at];
   };
-  weights(0, wl[0], wu[0]);
-  double yf[2][2], cf[2][2], ef[2][2];
+  auto far = [&]() {
 #pragma unroll
-  for (int k = 0; k < SS - 1; ++k) {
-    const double* pe = pe0 + 2 * k * TP;
-    const double* pc = pc0 + 2 * k;
-    const double2 e0 = *reinterpret_cast<const double2*>(pe);
-    const double2 e1 = *reinterpret_cast<const double2*>(pe + TP);
-    const double2 c0 = *reinterpret_cast<const double2*>(pc);
-    const double2 c1 = *reinterpret_cast<const double2*>(pc + TP);
-    // (LDS serves a wave's requests in order: the weight reads go out right
-    // behind the source reads, so that they are done before this step's
-    // writes and the next step's source reads)
-    __builtin_amdgcn_sched_barrier(0);
-    if (k + 1 < SS - 1) weights(k + 1, wl[(k + 1) & 1], wu[(k + 1) & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-    const double2 l0 = wl[k & 1][0], l1 = wl[k & 1][1];
-    const double2 v0 = wu[k & 1][0], v1 = wu[k & 1][1];
-    Dc[0][0] = fma(l0.y, e1.x, fma(l0.x, e0.x, Dc[0][0]));
-    Dc[0][1] = fma(l0.y, e1.y, fma(l0.x, e0.y, Dc[0][1]));
-    Dc[1][0] = fma(l1.y, e1.x, fma(l1.x, e0.x, Dc[1][0]));
-    Dc[1][1] = fma(l1.y, e1.y, fma(l1.x, e0.y, Dc[1][1]));
-    Rc[0][0] = fma(c0.y, v1.x, fma(c0.x, v0.x, Rc[0][0]));
-    Rc[0][1] = fma(c0.y, v1.y, fma(c0.x, v0.y, Rc[0][1]));
-    Rc[1][0] = fma(c1.y, v1.x, fma(c1.x, v0.x, Rc[1][0]));
-    Rc[1][1] = fma(c1.y, v1.y, fma(c1.x, v0.y, Rc[1][1]));
-    // The in-block chain, with every term that does not wait for this step's
-    // errors formed first. With D, R the accumulated feedback and
-    // C = D + E (L has a unit diagonal):
-    //   y00 = R00 + D00
-    //   y01 = R01 + D01 + u01 C00          = k01 + u01 e00
-    //   y10 = R10 + D10 + l10 e00          = k10 + l10 e00
-    //   y11 = R11 + D11 + l10 e01 + u01 C10
-    //       = k11 + u01 l10 e00 + l10 e01 + u01 e10
-    const double y00 = Rc[0][0] + Dc[0][0];
-    const double k01 = fma(Dc[0][0], u01, Rc[0][1] + Dc[0][1]);
-    const double k10 = Rc[1][0] + Dc[1][0];
-    const double k11 = fma(Dc[1][0], u01, Rc[1][1] + Dc[1][1]);
-    const double e00 = rint(y00) - y00;
-    const double y01 = fma(e00, u01, k01);
-    const double y10 = fma(e00, l10, k10);
-    const double m11 = fma(e00, ul, k11);
-    const double e01 = rint(y01) - y01;
-    const double e10 = rint(y10) - y10;
-    const double y11 = fma(e10, u01, fma(e01, l10, m11));
-    const double e11 = rint(y11) - y11;
-    const double c00 = Dc[0][0] + e00;
-    const double c01 = Dc[0][1] + e01;
-    const double c10 = fma(l10, e00, Dc[1][0]) + e10;
-    const double c11 = fma(l10, e01, Dc[1][1]) + e11;
-    *reinterpret_cast<double2*>(eown) = double2{e00, e01};
-    *reinterpret_cast<double2*>(eown + TP) = double2{e10, e11};
-    *reinterpret_cast<double2*>(cown) = double2{c00, c01};
-    *reinterpret_cast<double2*>(cown + TP) = double2{c10, c11};
-    if (k == SS - 2) {
-      yf[0][0] = y00; yf[0][1] = y01; yf[1][0] = y10; yf[1][1] = y11;
-      cf[0][0] = c00; cf[0][1] = c01; cf[1][0] = c10; cf[1][1] = c11;
-      ef[0][0] = e00; ef[0][1] = e01; ef[1][0] = e10; ef[1][1] = e11;
-    }
+    for (int q = 0; q < NO; ++q) (q & 1 ? d1 : d0) = mfma4(ev[q], lb[q], q & 1 ? d1 : d0);
+  };
+  auto near = [&]() {
+#pragma unroll
+    for (int q = NO; q < NQ; ++q) (q & 1 ? d1 : d0) = mfma4(ev[q], lb[q], q & 1 ? d1 : d0);
+  };
+  // steps 0, 1, 2: no block of the band is finished early enough
+#pragma unroll 1
+  for (int k = 0; k < 3; ++k) {
+    begin(0);
+    if (W > 0) wait_count(up, k + BANDB, above, bad);
+#pragma unroll
+    for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TX];
+    far();
+    near();
+    if (W > 0) *pt = d0 + d1;
+    store_count(&sm.prep[W], k + 1);
+    pu += BS * TE + BS;
+    pm += BS;
+    pt += BS;
+    pe += BS;
+    p3 += BS;
   }
-
-  // hand-off to the band below, then the global outputs
-  __hip_atomic_store(&sm.done[w], C + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  begin(0);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    *reinterpret_cast<double2*>(b.Et + r_idx(br + i, uc + 2 * q)) = double2{ef[i][0], ef[i][1]};
-    *reinterpret_cast<double2*>(b.Ct + s_idx(br + i, uc + 2 * q)) = double2{cf[i][0], cf[i][1]};
-  }
-  const int64_t cs = a.cstep;
-  if (b.interior) {
-    // every entry of the tile lies inside the matrix: no bounds checks, and
-    // the range check folded into one test per entry (NaN fails it too)
-    bool ok = true;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      int32_t* zr = b.zr[i] + uc * cs;
-      T* yr = b.yr[i] ? (T*)b.yr[i] + uc * cs : nullptr;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const double yv = yf[i][j];
-        ok = ok && yv >= -2147483648.5 && yv < 2147483647.5;
-        const double zc = fmin(fmax(rint(yv), -2147483648.0), 2147483647.0);
-        zr[j * cs] = (int32_t)zc;
-        if (yr) yr[j * cs] = (T)yv;
-        part = fma(ef[i][j] * ef[i][j], b.dl[i] * dc[j], part);
-      }
+  for (int d = 0; d < ND; ++d) uv[d] = pu[BS * d];
+  far();
+#pragma unroll 1
+  for (int k = 3; k < STEPS; ++k) {
+    asm volatile("" : "+v"(pu), "+v"(pm), "+v"(pt), "+v"(pe), "+v"(p3));
+    if (W > 0) {
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(above) < min(k + BANDB, STEPS), 0))
+        wait_count(up, min(k + BANDB, STEPS), above, bad);
     }
-    if (!ok) {
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) < k - 2, 0)) wait_count(&sm.done[W], k - 2, seen, bad);
+    asm volatile("" ::: "memory");
+    const double ct = pt[-3 * BS], e3 = *p3;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TX];
+    __builtin_amdgcn_sched_barrier(0);
+    acc[0] = mfma4(ct, uv[0], acc[1]);
+    d1 = mfma4(e3, la3, d1);
+    near();
+    *pm = x + acc[0];
+    *pt = d0 + d1;
+    store_count(&sm.prep[W], k + 1);
+    // the next step's operands
+    begin(BS);
+    uv[0] = pu[BS * TE + BS];
+    seen = load_count(&sm.done[W]);
+    if (W > 0) above = load_count(up);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // the feedback on the steps further ahead; blocks past the tile's last
+    // column are left out
 #pragma unroll
-        for (int j = 0; j < 2; ++j) bad |= isfinite(yf[i][j]) ? 0 : FLAG_NONFINITE;
-      if (!(bad & FLAG_NONFINITE)) bad |= FLAG_OVERFLOW;
-    }
-  } else {
-    T* Y = (T*)a.Y;
+    for (int c0 = 1; c0 < ND; c0 += 4) {
+      if (k + c0 < STEPS) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int gi = b.gi0 + br + i;
-      const int gj = b.gj0 + uc + 2 * q;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const double yv = yf[i][j];
-        const double z = rint(yv);
-        if (gi < a.m && gj + j < a.n) {
-          if (!isfinite(yv)) bad |= FLAG_NONFINITE;
-          else if (z < -2147483648.0 || z > 2147483647.0) bad |= FLAG_OVERFLOW;
-          const double zc = fmin(fmax(z, -2147483648.0), 2147483647.0);
-          a.Z[(int64_t)gi * a.ldz + (gj + j) * cs] = isfinite(zc) ? (int32_t)zc : 0;
-          if (Y) Y[(int64_t)gi * a.ldy + (gj + j) * cs] = (T)yv;
-          part = fma(ef[i][j] * ef[i][j], b.dl[i] * dc[j], part);
+        for (int d = c0; d < c0 + 4 && d < ND; ++d) {
+          acc[d] = mfma4(ct, uv[d], acc[d + 1]);
+          uv[d] = pu[BS * TE + BS + BS * d];
         }
       }
     }
+    far();
+    pu += BS * TE + BS;
+    pm += BS;
+    pt += BS;
+    pe += BS;
+    p3 += BS;
   }
 }
 
-// Sweep of one tile. Wave w owns the 16-row band 16w .. 16w+15 and sweeps its
-// four 16 x 16 sub-tiles left to right, one wave per sub-tile, so that the
-// per-anti-diagonal exchange stays inside the wave (LDS, no workgroup
-// barrier). Sub-tile (w, c) starts when the band above has finished
-// sub-tile c; the feedback from the finished sub-tiles above and to the left
-// is added first as two small MFMA products. Lane l owns the 2 x 2 block at
-// band rows 2p, 2p+1 (p = l >> 3) and sub-tile columns 2q, 2q+1 (q = l & 7):
-// eight consecutive lanes read eight different column pairs of a factor row,
-// which keeps the LDS window reads free of bank conflicts.
+// Rows r0 .. r0 + n - 1 of a finished tile by one wave, a lane per column: Z,
+// Y, E, C and the lane's part of the objective.
+template <typename T>
+__device__ __forceinline__ void sweep_output(const StageArgs& a, const SweepSmem& sm, int I, int J, int r0,
+                                             int n, double du, bool interior, double& part, int& bad) {
+  const int l = threadIdx.x & 63;
+  const int64_t gj = (int64_t)J * TB + l;
+  double* const E = a.E + tile_off(I, J, a.NT);
+  double* const C = a.C + tile_off(I, J, a.NT);
+  const bool in = gj < a.n;
+#pragma unroll 2
+  for (int i = 0; i < n; ++i) {
+    const int rr = r0 + i;
+    const int64_t gi = (int64_t)I * TB + rr;
+    const int at = PAD + rr * TX + l;
+    const double y = sm.Xs[at], e = sm.Et[at];
+    E[r_idx(rr, l)] = e;
+    C[s_idx(rr, l)] = sm.Ct[PAD + rr * TE + l];
+    if (interior || (in && gi < a.m)) {
+      // (a NaN fails the range test, too)
+      if (!(y >= -2147483648.5 && y < 2147483647.5)) bad |= isfinite(y) ? FLAG_OVERFLOW : FLAG_NONFINITE;
+      const double z = fmin(fmax(rint(y), -2147483648.0), 2147483647.0);
+      a.Z[gi * a.ldz + gj * a.cstep] = (int32_t)z;
+      if (a.Y) ((T*)a.Y)[gi * a.ldy + gj * a.cstep] = (T)y;
+      part = fma(e * e, a.dL[gi] * du, part);
+    }
+  }
+}
+
+// 64 x 64 blocks by the 512 threads of a work group: element e = t + 512 s.
+__device__ __forceinline__ void sweep_load(const double* p, double (&v)[8]) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) v[s] = p[threadIdx.x + ST * s];
+}
+// operands of a neighbour product: a (in S order) and b (in R order), both
+// k-major in LDS
+__device__ __forceinline__ void sweep_stage(Stage64& g, const double (&a)[8], const double (&b)[8]) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int e = threadIdx.x + ST * s;
+    g.a[((e >> 11) << 5) + (e & 31)][(e >> 5) & 63] = a[s];
+    g.b[e >> 6][e & 63] = b[s];
+  }
+}
+// acc[u] += rows 32 (w / 4) + 16 u .., columns 16 (w % 4) .. of the staged product
+__device__ __forceinline__ void sweep_product(d4 (&acc)[2], const Stage64& g) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int rb = 32 * (w >> 2) + (l & 15), cb = 16 * (w & 3) + (l & 15);
+#pragma unroll
+  for (int kk = 0; kk < TB / 4; ++kk) {
+    const int k = 4 * kk + (l >> 4);
+    const double a0 = g.a[k][rb], a1 = g.a[k][rb + 16], b0 = g.b[k][cb];
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1], 0, 0, 0);
+  }
+}
+
+// Sweep of one tile. The deferred feedback (P, R), X and the two neighbour
+// products (L[I][I-1] E[I-1][J] and C[I][J-1] U[J-1][J]) are summed in the
+// accumulator layout of the products and go to LDS, where the bands' sweeps
+// start from them.
 template <typename T>
 __device__ void run_sweep(const StageArgs& a, int I, int J, SweepSmem& sm) {
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
-  const int p = l >> 3, q = l & 7;
-  const int br = SS * w + 2 * p;  // tile row of the lane's first row
   const int gi0 = I * TB, gj0 = J * TB;
   const T* X = (const T*)a.X;
 
-  // every global load of the prologue is issued before any is used, in the
-  // order they are needed: the factor blocks, the operands of the two
-  // neighbour products, then X and the accumulated feedback
-  double lv[16], uv[16], ga[16], gb[16], gc[16], gd[16];
-  load_blk_s(a.L + tile_off(I, I, a.MT), lv);
-  load_blk(a.U + tile_off(J, J, a.NT), TB, uv);
+  // every global load of the prologue is issued before any is used
+  double uv[8], ga[8], gb[8], gc[8], gd[8];
   if (I >= 1) {
-    load_blk_s(a.L + tile_off(I, I - 1, a.MT), ga);
-    load_blk(a.E + tile_off(I - 1, J, a.NT), TB, gb);
+    sweep_load(a.L + tile_off(I, I - 1, a.MT), ga);
+    sweep_load(a.E + tile_off(I - 1, J, a.NT), gb);
   }
   if (J >= 1) {
-    load_blk_s(a.C + tile_off(I, J - 1, a.NT), gc);
-    load_blk(a.U + tile_off(J - 1, J, a.NT), TB, gd);
+    sweep_load(a.C + tile_off(I, J - 1, a.NT), gc);
+    sweep_load(a.U + tile_off(J - 1, J, a.NT), gd);
   }
-  // the off-diagonal entries of the lane's 2 x 2 diagonal factor blocks
-  const double l10v = a.L[tile_off(I, I, a.MT) + s_idx(br + 1, br)];
-  double u01v[4];
+  sweep_load(a.U + tile_off(J, J, a.NT), uv);
+  d4 accR[2], accD[2];
+  const double* const Rt = a.R + tile_off(I, J, a.NT);
+  const double* const Pt = a.P + tile_off(I, J, a.NT);
+  const int ar = 32 * (w >> 2) + (l >> 4), ac = 16 * (w & 3) + (l & 15);  // + 16 u + 4 q rows
 #pragma unroll
-  for (int c = 0; c < 4; ++c) u01v[c] = a.U[tile_off(J, J, a.NT) + r_idx(SS * c + 2 * q, SS * c + 2 * q + 1)];
-  double Dn[4][2][2], Rt[4][2][2], dl[2], du[4][2];
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) dl[i] = a.dL[gi0 + br + i];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) du[c][j] = a.dU[gj0 + SS * c + 2 * q + j];
-  // X, then the accumulated right (R, from tile column 2 on) and down (P,
-  // from tile row 2 on) feedback; each group is issued as one batch
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        Rt[c][i][j] = load_x<T>(X, a.ldx, a.cstep, gi0 + br + i, gj0 + SS * c + 2 * q + j, a.m, a.n);
-  double2 rv[4][2], pv[4][2];
+    for (int q = 0; q < 4; ++q) {
+      const int rr = ar + 16 * u + 4 * q;
+      accR[u][q] = load_x<T>(X, a.ldx, a.cstep, gi0 + rr, gj0 + ac, a.m, a.n);
+      accD[u][q] = 0.0;
+    }
   if (J >= 2) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        rv[c][i] = *reinterpret_cast<const double2*>(a.R + tile_off(I, J, a.NT) + r_idx(br + i, SS * c + 2 * q));
-  } else {
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) rv[c][i] = double2{0.0, 0.0};
+      for (int q = 0; q < 4; ++q) accR[u][q] += Rt[r_idx(ar + 16 * u + 4 * q, ac)];
   }
   if (I >= 2) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        pv[c][i] = *reinterpret_cast<const double2*>(a.P + tile_off(I, J, a.NT) + r_idx(br + i, SS * c + 2 * q));
-  } else {
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) pv[c][i] = double2{0.0, 0.0};
+      for (int q = 0; q < 4; ++q) accD[u][q] = Pt[r_idx(ar + 16 * u + 4 * q, ac)];
   }
-  // the factor blocks go to LDS with their 2 x 2 diagonal blocks zeroed: the
-  // block sweep takes the one off-diagonal entry of each (l10, u01) from a
-  // register, and the zeros make the lane's own block a zero-weight source
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    const int e = t + NT * s, r = e >> 6, x = e & 63;
-    const bool dg = (r >> 1) == (x >> 1);
-    sm.Ls[r][x] = dg ? 0.0 : lv[s];
-    sm.Us[r][x] = dg ? 0.0 : uv[s];
-  }
-  if (t < TB) {
-    *reinterpret_cast<double2*>(&sm.Ls[t][TB]) = double2{0.0, 0.0};
-    sm.Us[TB][t] = 0.0;
-    sm.Us[TB + 1][t] = 0.0;
-  }
-  if (t < 4) sm.done[t] = 0;
+  const double du = a.dU[gj0 + l];
 
-  // feedback of the neighbouring tiles: L[I][I-1] E[I-1][J] and C[I][J-1]
-  // U[J-1][J]; the accumulated feedback (P, R) is added first, as before
-  // either product
-  Acc acc;
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      Dn[c][i][0] = pv[c][i].x;
-      Dn[c][i][1] = pv[c][i].y;
-    }
-  if (I >= 1) {
-    acc.zero();
-    put_a(sm.x.g, ga);
-    put_b(sm.x.g, gb);
-    __syncthreads();
-    mma_blk(acc, sm.x.g);
-    __syncthreads();
-    acc_to_lds<TB + 1>(acc, sm.x.T);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) Dn[c][i][j] += sm.x.T[br + i][SS * c + 2 * q + j];
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      Rt[c][i][0] += rv[c][i].x;
-      Rt[c][i][1] += rv[c][i].y;
-    }
-  if (J >= 1) {
-    acc.zero();
-    __syncthreads();
-    put_a(sm.x.g, gc);
-    put_b(sm.x.g, gd);
-    __syncthreads();
-    mma_blk(acc, sm.x.g);
-    __syncthreads();
-    acc_to_lds<TB + 1>(acc, sm.x.T);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) Rt[c][i][j] += sm.x.T[br + i][SS * c + 2 * q + j];
-  }
-  __syncthreads();
-  // Et / Ct start at zero, their padding columns included: the block sweep
-  // reads (zero-weighted) source blocks before they are written, and its
-  // C-source reads of the first sub-tile reach back into the padding of the
-  // row before; every wave zeroes its band, and the barrier makes the whole
-  // arrays zero before any wave sweeps
+  // U_JJ, unit upper, and its zero columns
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
-    const int e = l + 64 * s, r = SS * w + (e >> 5), x = 2 * (e & 31);
-    *reinterpret_cast<double2*>(&sm.x.t.Et[r][x]) = double2{0.0, 0.0};
-    *reinterpret_cast<double2*>(&sm.x.t.Ct[r][x]) = double2{0.0, 0.0};
+    const int e = t + ST * s, r = e >> 6, x = e & 63;
+    sm.Us[r * TE + x] = x > r ? uv[s] : x == r ? 1.0 : 0.0;
   }
-  if (l < 2 * SS) {
-    double(*arr)[TP] = l < SS ? sm.x.t.Et : sm.x.t.Ct;
-    *reinterpret_cast<double2*>(&arr[SS * w + (l & (SS - 1))][TB]) = double2{0.0, 0.0};
+  for (int e = t; e < TB * PAD; e += ST) sm.Us[(e / PAD) * TE + TB + e % PAD] = 0.0;
+  if (t < BANDS) sm.done[t] = sm.prep[t] = 0;
+  if (I >= 1) {
+    sweep_stage(sm.g, ga, gb);
+    __syncthreads();
+    sweep_product(accD, sm.g);
+    __syncthreads();
   }
-  Band bd;
-  bd.w = w; bd.l = l; bd.p = p; bd.q = q; bd.br = br; bd.gi0 = gi0; bd.gj0 = gj0;
-  bd.Et = a.E + tile_off(I, J, a.NT);
-  bd.Ct = a.C + tile_off(I, J, a.NT);
-  bd.l10 = l10v;
+  if (J >= 1) {
+    sweep_stage(sm.g, gc, gd);
+    __syncthreads();
+    sweep_product(accR, sm.g);
+    __syncthreads();
+  }
 #pragma unroll
-  for (int c = 0; c < 4; ++c) bd.u01[c] = u01v[c];
-  bd.dl[0] = dl[0];
-  bd.dl[1] = dl[1];
-  bd.interior = gi0 + TB <= a.m && gj0 + TB <= a.n;
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    bd.zr[i] = a.Z + (int64_t)(gi0 + br + i) * a.ldz + (int64_t)(gj0 + 2 * q) * a.cstep;
-    bd.yr[i] = a.Y ? (void*)((T*)a.Y + (int64_t)(gi0 + br + i) * a.ldy + (int64_t)(gj0 + 2 * q) * a.cstep)
-                   : nullptr;
-  }
+    for (int q = 0; q < 4; ++q) {
+      sm.Xs[PAD + (ar + 16 * u + 4 * q) * TX + ac] = accR[u][q];
+      sm.Ct[PAD + (ar + 16 * u + 4 * q) * TE + ac] = accD[u][q];
+    }
+  // the zero columns; no errors yet (a product with a zero weight must not meet
+  // a NaN in memory that nobody has written)
+  for (int e = t; e < (TB + 1) * PAD; e += ST) sm.Ct[(e / PAD) * TE + e % PAD] = 0.0;
+  for (int e = t; e < (TB + 1) * 16; e += ST) sm.Xs[e < 12 ? e : (e / 16) * TX + e % 16 - (TX - TB - PAD)] = 0.0;
+  for (int e = t; e < TXN / 2; e += ST) *reinterpret_cast<double2*>(&sm.Et[2 * e]) = double2{0.0, 0.0};
   __syncthreads();
 
   double part = 0.0;
   int bad = 0;
-  sub_tile<T, 0>(a, sm, bd, Dn[0], Rt[0], du[0], part, bad);
-  sub_tile<T, 1>(a, sm, bd, Dn[1], Rt[1], du[1], part, bad);
-  sub_tile<T, 2>(a, sm, bd, Dn[2], Rt[2], du[2], part, bad);
-  sub_tile<T, 3>(a, sm, bd, Dn[3], Rt[3], du[3], part, bad);
+  const double* const Lt = a.L + tile_off(I, I, a.MT);
+  // (the second wave of a band runs on the SIMD of a band two further down,
+  // which has half of its steps at another time)
+  const int band = (w < BANDS ? w : w + 2) & (BANDS - 1);
+  if (w < BANDS) {
+    __builtin_amdgcn_s_setprio(2);
+    if (band == 0) sweep_band<0>(Lt, sm, l, bad);
+    else if (band == 1) sweep_band<1>(Lt, sm, l, bad);
+    else if (band == 2) sweep_band<2>(Lt, sm, l, bad);
+    else sweep_band<3>(Lt, sm, l, bad);
+    __builtin_amdgcn_s_setprio(0);
+  } else {
+    if (band == 0) prepare_band<0>(Lt, sm, l, bad);
+    else if (band == 1) prepare_band<1>(Lt, sm, l, bad);
+    else if (band == 2) prepare_band<2>(Lt, sm, l, bad);
+    else prepare_band<3>(Lt, sm, l, bad);
+  }
+  // the bands' outputs: half a band by each of its two waves, the last band's
+  // by all
+  const bool interior = gi0 + TB <= a.m && gj0 + TB <= a.n;
+  constexpr int BR = BS * BANDB;
+  if (band < BANDS - 1) {
+    int seen = 0;
+    wait_count(&sm.done[band], STEPS, seen, bad);
+    sweep_output<T>(a, sm, I, J, BR * band + (w < BANDS ? 0 : BR / 2), BR / 2, du, interior, part, bad);
+  }
+  __syncthreads();
+  sweep_output<T>(a, sm, I, J, BR * (BANDS - 1) + BR / 8 * w, BR / 8, du, interior, part, bad);
 
   if (bad) raise_flag(a.flags, bad);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off, 64);
   if (l == 0) sm.red[w] = part;
   __syncthreads();
-  if (t == 0) a.objp[I * a.NT + J] = (sm.red[0] + sm.red[1]) + (sm.red[2] + sm.red[3]);
+  if (t == 0)
+    a.objp[I * a.NT + J] = ((sm.red[0] + sm.red[1]) + (sm.red[2] + sm.red[3])) +
+                           ((sm.red[4] + sm.red[5]) + (sm.red[6] + sm.red[7]));
 }
 
 template <typename T>
-__global__ __launch_bounds__(NT) void k_stage(StageArgs a) {
+__global__ __launch_bounds__(ST) void k_stage(StageArgs a) {
   __shared__ StageSmem sm;
   const int b = blockIdx.x;
   if (b < a.nsweep) {
@@ -873,7 +902,7 @@ __device__ __forceinline__ StageArgs batch_args(const BatchProb& q, int* flags) 
 }
 
 template <typename T>
-__global__ __launch_bounds__(NT) void k_stage_batch(BatchLaunch bl) {
+__global__ __launch_bounds__(ST) void k_stage_batch(BatchLaunch bl) {
   __shared__ StageSmem sm;
   const int b = blockIdx.x;
   // the last p with off[p] <= b (problems without a stage k own no block)
@@ -1309,7 +1338,7 @@ static gptq2d_status round_typed(const Factors& f, const void* X, int64_t ldx, i
     }
     // with timing on, the two events take the start and end time stamps of
     // the dispatch itself (no marker packets between the launches)
-    hipExtLaunchKernelGGL(k_stage<T>, dim3(a.nsweep + ntasks), dim3(NT), 0, s, e0, e1, 0, a);
+    hipExtLaunchKernelGGL(k_stage<T>, dim3(a.nsweep + ntasks), dim3(ST), 0, s, e0, e1, 0, a);
   }
   if (objective)
     hipLaunchKernelGGL(k_obj_reduce, dim3(1), dim3(NT), 0, s, ws.objp, f.MT * f.NT, objective);
@@ -1372,7 +1401,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
       }
       bl.off[cnt] = tot;
       bl.stage = k;
-      hipLaunchKernelGGL(k_stage_batch<T>, dim3(tot), dim3(NT), 0, s, bl);
+      hipLaunchKernelGGL(k_stage_batch<T>, dim3(tot), dim3(ST), 0, s, bl);
     }
   }
   if (objective) hipLaunchKernelGGL(k_obj_reduce_batch, dim3(count), dim3(NT), 0, s, desc, objective);
