@@ -208,10 +208,10 @@ gptq2d_status gptq2d_factor_check(gptq2d_factors_t f, void* stream) {
   if (!f) return fail(GPTQ2D_ERR_INVALID_ARG, "handle is NULL");
   hipError_t e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  int flags = 0;
-  e = hipMemcpy(&flags, f->flags, sizeof(int), hipMemcpyDeviceToHost);
+  int flags[2] = {0, 0};
+  e = hipMemcpy(flags, f->flags, sizeof(flags), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
-  if (flags & FLAG_SINGULAR)
+  if ((flags[0] | flags[1]) & FLAG_SINGULAR)
     return fail(GPTQ2D_ERR_SINGULAR, "a Gram pivot was not positive and finite (A or B singular)");
   return GPTQ2D_OK;
 }

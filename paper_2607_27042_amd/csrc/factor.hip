@@ -40,7 +40,7 @@ struct Side {
 
 struct FacArgs {
   Side s[2];
-  int* flags;
+  int* flags; // two error words: a problem of one block has one per side
   int* genv;  // Gram envelopes and work plan (GramView)
   int rev;    // reverse order: the index-reversed problem (A P, P B), so no reversal below
 };
@@ -197,6 +197,7 @@ __global__ __launch_bounds__(NT) void k_gram(FacArgs f0, const T* A0, int64_t ld
   const int bid = bat_block<BAT>(bc);
   const int rev = BAT ? (int)pb->rev : f0.rev;
   const int t0 = (sides & 1) ? f.s[0].nb * (f.s[0].nb + 1) / 2 : 0;
+  if (bid == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
   int bp, bq;
   if (bid < t0) {
     tri_index(bid, bp, bq);
@@ -204,6 +205,107 @@ __global__ __launch_bounds__(NT) void k_gram(FacArgs f0, const T* A0, int64_t ld
   } else {
     tri_index(bid - t0, bp, bq);
     gram_tile<T, 1>(f.s[1], B, ldb, bp, bq, st, rev);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Gram of a small side on 32 x 32 tiles, one work group each, straight from the
+// basis. A small Gram is bound by the latency of its contraction, not by its
+// flops: on 128 x 128 tiles the 512 side of a 512 x 384 problem has ten work
+// groups that contract 16 chunks one after another (83 us, with 25 us of
+// launches around them); 32 x 32 tiles give 136, each of them an eighth of the
+// matrix work per 64-deep block. Every wave forms one 16 x 16 block; the next
+// block's loads are in flight during the products (one barrier per block, two
+// LDS buffers).
+// ---------------------------------------------------------------------------
+
+constexpr int GT = 32;       // tile edge
+constexpr int GTS = GT + 1;  // LDS row stride (odd: transposed writes spread over the banks)
+struct Gram32 {
+  double a[TB][GTS];  // a[k][i] = S(k, 32 bp + i)
+  double b[TB][GTS];
+};
+
+template <typename T, int SIDE>
+__device__ __forceinline__ void gram32_load(const T* S, int64_t ld, int d, int i0, int k0, T (&v)[8], int rev) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int e = threadIdx.x + NT * s;
+    // side 0: A[k][d-1-i], coalesced along i; side 1: B[d-1-i][k], along k
+    const int i = i0 + (SIDE == 0 ? e & 31 : e >> 6), k = k0 + (SIDE == 0 ? e >> 5 : e & 63);
+    const bool ok = k < d && i < d;
+    const int idx = rev ? i : d - 1 - i;
+    const T x = S[!ok ? 0 : SIDE == 0 ? (int64_t)k * ld + idx : (int64_t)idx * ld + k];
+    v[s] = ok ? x : (T)0;
+  }
+}
+template <typename T, int SIDE>
+__device__ __forceinline__ void gram32_put(double (*g)[GTS], const T (&v)[8]) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int e = threadIdx.x + NT * s;
+    if (SIDE == 0) g[e >> 5][e & 31] = (double)v[s];
+    else g[e & 63][e >> 6] = (double)v[s];
+  }
+}
+
+template <typename T, int SIDE>
+__device__ void gram32_tile(const Side& sd, const T* S, int64_t ld, int bp, int bq, Gram32* buf, int rev) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int rb = 16 * (w >> 1) + (l & 15), cb = 16 * (w & 1) + (l & 15);
+  const bool diag = bp == bq;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  T va[8], vb[8];
+  gram32_load<T, SIDE>(S, ld, sd.d, bp * GT, 0, va, rev);
+  if (!diag) gram32_load<T, SIDE>(S, ld, sd.d, bq * GT, 0, vb, rev);
+  const int nk = (sd.d + TB - 1) / TB;
+  for (int kb = 0; kb < nk; ++kb) {
+    Gram32& g = buf[kb & 1];
+    gram32_put<T, SIDE>(g.a, va);
+    if (!diag) gram32_put<T, SIDE>(g.b, vb);
+    __syncthreads();
+    if (kb + 1 < nk) {
+      gram32_load<T, SIDE>(S, ld, sd.d, bp * GT, (kb + 1) * TB, va, rev);
+      if (!diag) gram32_load<T, SIDE>(S, ld, sd.d, bq * GT, (kb + 1) * TB, vb, rev);
+    }
+    double(*gb)[GTS] = diag ? g.a : g.b;
+#pragma unroll
+    for (int kk = 0; kk < TB / 4; ++kk) {
+      const int k = 4 * kk + (l >> 4);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(g.a[k][rb], gb[k][cb], acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int pp = bp * GT + 16 * (w >> 1) + 4 * r + (l >> 4), qq = bq * GT + cb;
+    double val = acc[r];
+    if (pp >= sd.d || qq >= sd.d) val = pp == qq ? 1.0 : 0.0;
+    sd.gr[(int64_t)pp * sd.dp + qq] = val;
+  }
+}
+
+// (`sides` as for k_gram; only the lower 32 x 32 tiles are written, which is
+// all that is read of a Gram)
+template <typename T, bool BAT>
+__global__ __launch_bounds__(NT) void k_gram32(FacArgs f0, const T* A0, int64_t lda0, const T* B0,
+                                               int64_t ldb0, int sides, BatchCtx bc) {
+  __shared__ Gram32 buf[2];
+  const FacProb* pb = bat_prob<BAT>(bc);
+  const FacArgs& f = BAT ? pb->base->f : f0;
+  const T* A = BAT ? (const T*)pb->A : A0;
+  const T* B = BAT ? (const T*)pb->B : B0;
+  const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
+  const int bid = bat_block<BAT>(bc);
+  const int rev = BAT ? (int)pb->rev : f0.rev;
+  const int n0 = f.s[0].dp / GT, t0 = (sides & 1) ? n0 * (n0 + 1) / 2 : 0;
+  if (bid == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
+  int bp, bq;
+  if (bid < t0) {
+    tri_index(bid, bp, bq);
+    gram32_tile<T, 0>(f.s[0], A, lda, bp, bq, buf, rev);
+  } else {
+    tri_index(bid - t0, bp, bq);
+    gram32_tile<T, 1>(f.s[1], B, ldb, bp, bq, buf, rev);
   }
 }
 
@@ -320,6 +422,7 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
   const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
   const int n0 = (sides & 1) ? (f.s[0].d / TB) * (f.s[0].d / TB) : 0;
   int b = bat_block<BAT>(bc);
+  if (b == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
   const int side = b < n0 ? 0 : 1;
   if (side == 1) b -= n0;
   const Side& sd = f.s[side];
@@ -643,7 +746,14 @@ static GramPlan gram_plan(int m, int n, int fast, int cus) {
   return pl;
 }
 
-static int fast_sides(int m, int n) { return (m % 128 == 0 ? 1 : 0) | (n % 128 == 0 ? 2 : 0); }
+// Up to this dimension a side's Gram runs on 32 x 32 tiles (512 x 384: the Gram's
+// launches 102 -> 14 us; the 136 tiles of a 1024 side still leave the 128 x 128
+// route with fewer work groups than compute units).
+constexpr int kSmallGram = 1024;
+
+static int fast_sides(int m, int n) {
+  return (m > kSmallGram && m % 128 == 0 ? 1 : 0) | (n > kSmallGram && n % 128 == 0 ? 2 : 0);
+}
 
 size_t gram_part_doubles(int m, int n, int cus) {
   const int fast = fast_sides(m, n);
@@ -822,29 +932,14 @@ struct DiagSmem {
   double Tm[4][DS][DS + 1];
 };
 
-// Diagonal block kb of one side by one work group: Cholesky factor in place
-// (gr) and its inverse into dinv.
-__device__ void diag_tile(const Side& sd, int kb, int* flags, DiagSmem& ds) {
+// The block in ds.Am (zero above the diagonal; ds.Wm zero) by one work group:
+// Cholesky factor in place, its inverse in ds.Wm.
+__device__ void diag_core(int* flags, DiagSmem& ds) {
   constexpr int LD = DLD;
   double(*Am)[LD] = ds.Am;
   double(*Wm)[LD] = ds.Wm;
   double(*Tm)[DS][DS + 1] = ds.Tm;
-  const int t = threadIdx.x, w = t >> 6;
-  double* blk = sd.gr + (int64_t)kb * TB * sd.dp + (int64_t)kb * TB;
-  {
-    double x[16];
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const int e = t + NT * s;
-      x[s] = blk[(int64_t)(e >> 6) * sd.dp + (e & 63)];
-    }
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const int e = t + NT * s, r = e >> 6, c = e & 63;
-      Am[r][c] = (c <= r) ? x[s] : 0.0;
-      Wm[r][c] = 0.0;
-    }
-  }
+  const int w = threadIdx.x >> 6;
   __syncthreads();
   // off-diagonal block row i of the inverse, block (i, w) by wave w < i:
   // W_iw = -W_ii (sum_{m=w}^{i-1} L_im W_mw)
@@ -891,13 +986,106 @@ __device__ void diag_tile(const Side& sd, int kb, int* flags, DiagSmem& ds) {
   }
   if (w < 3) wrow(3);
   __syncthreads();
+}
+
+// The factored diagonal block kb of one side: the factor into gr, its inverse
+// into dinv.
+__device__ __forceinline__ void diag_store(const Side& sd, int kb, const DiagSmem& ds) {
+  double* blk = sd.gr + (int64_t)kb * TB * sd.dp + (int64_t)kb * TB;
   double* dv = sd.dinv + (int64_t)kb * TB * TB;
 #pragma unroll
   for (int s = 0; s < 16; ++s) {
-    const int e = t + NT * s, r = e >> 6, c = e & 63;
-    blk[(int64_t)r * sd.dp + c] = Am[r][c];
-    dv[e] = Wm[r][c];
+    const int e = threadIdx.x + NT * s, r = e >> 6, c = e & 63;
+    blk[(int64_t)r * sd.dp + c] = ds.Am[r][c];
+    dv[e] = ds.Wm[r][c];
   }
+}
+
+// Diagonal block kb of one side by one work group.
+__device__ void diag_tile(const Side& sd, int kb, int* flags, DiagSmem& ds) {
+  const int t = threadIdx.x;
+  double* blk = sd.gr + (int64_t)kb * TB * sd.dp + (int64_t)kb * TB;
+  {
+    double x[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int e = t + NT * s;
+      x[s] = blk[(int64_t)(e >> 6) * sd.dp + (e & 63)];
+    }
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int e = t + NT * s, r = e >> 6, c = e & 63;
+      ds.Am[r][c] = (c <= r) ? x[s] : 0.0;
+      ds.Wm[r][c] = 0.0;
+    }
+  }
+  diag_core(flags, ds);
+  diag_store(sd, kb, ds);
+}
+
+// A problem of one block per side in one launch, a work group per side: Gram,
+// factor, inverse and normalisation (the formulas of k_finalize) without
+// leaving LDS. Five launches took 38 us for 64 x 64; their work is the 12 us
+// chain of the diagonal block.
+template <typename T, bool BAT>
+__global__ __launch_bounds__(NT) void k_one_block(FacArgs f0, const T* A0, int64_t lda0, const T* B0,
+                                                  int64_t ldb0, BatchCtx bc) {
+  __shared__ union {
+    Stage64 st;
+    DiagSmem d;
+  } sm;
+  __shared__ double sc[TB];
+  const FacProb* pb = bat_prob<BAT>(bc);
+  const FacArgs& f = BAT ? pb->base->f : f0;
+  const int side = bat_block<BAT>(bc), t = threadIdx.x;
+  const Side sd = f.s[side];
+  const int rev = BAT ? (int)pb->rev : f0.rev, d = sd.d;
+  // an error word per side: the other side's work group may run at any time
+  int* const flags = f.flags + side;
+  if (t == 0) {
+    flags[0] = 0;
+    __threadfence();
+  }
+  Acc acc;
+  acc.zero();
+  double r[16];
+  if (side == 0) {
+    gram_load<T, 0>(BAT ? (const T*)pb->A : A0, BAT ? pb->lda : lda0, d, 0, 0, r, rev);
+    put_ak(sm.st, r);
+    put_b(sm.st, r);
+  } else {
+    gram_load<T, 1>(BAT ? (const T*)pb->B : B0, BAT ? pb->ldb : ldb0, d, 0, 0, r, rev);
+    put_a(sm.st, r);
+    put_bt(sm.st, r);
+  }
+  __syncthreads();
+  mma_blk(acc, sm.st);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = acc_row(u, q), j = acc_col(v);
+        const double x = i >= d || j >= d ? (i == j ? 1.0 : 0.0) : acc.t[2 * u + v][q];
+        sm.d.Am[i][j] = j <= i ? x : 0.0;
+        sm.d.Wm[i][j] = 0.0;
+      }
+  diag_core(flags, sm.d);
+  if (t < TB) sc[t] = t < d ? sm.d.Am[d - 1 - t][d - 1 - t] : 1.0;  // of row / column t of the factor
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const int e = t + NT * s, i = e >> 6, j = e & 63;
+    double val = i == j ? 1.0 : 0.0;
+    if (i < d && j < d && i != j) {
+      if (side == 0) val = i > j ? sm.d.Wm[d - 1 - j][d - 1 - i] * sc[j] : 0.0;
+      else val = j > i ? sm.d.Wm[d - 1 - i][d - 1 - j] * sc[i] : 0.0;
+    }
+    sd.out[side == 0 ? s_idx(i, j) : r_idx(i, j)] = val;
+  }
+  if (t < TB) sd.dout[t] = t < d ? sc[t] * sc[t] : 1.0;
 }
 
 template <bool BAT>
@@ -977,7 +1165,8 @@ __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, in
 }
 
 // acc += sum over 64-deep blocks b of A_b op(B_b), A_b at pa + b*sa_, B_b at
-// pb + b*sb_; BT: B given transposed. Double-buffered through LDS.
+// pb + b*sb_; BT: B given transposed and the sum subtracted. Double-buffered
+// through LDS.
 template <int BT>
 __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_, const double* pb,
                             int64_t ldb, int64_t sb_, int nb, Stage64* st) {
@@ -986,6 +1175,10 @@ __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_
   load_blk(pb, ldb, rb);
   for (int b = 0; b < nb; ++b) {
     Stage64& s = st[b & 1];
+    if (BT) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ra[i] = -ra[i];
+    }
     put_a(s, ra);
     if (BT) put_bt(s, rb);
     else put_b(s, rb);
@@ -1030,30 +1223,32 @@ __global__ __launch_bounds__(NT) void k_update(FacArgs f0, UpdRange r, BatchCtx 
       ++bj;
     }
     const int bi = bj + b;
+    double* out = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)bj * TB;
+    // the sum starts from the old value, here and in the far update: its terms
+    // come in the order of the panels however they are grouped into launches,
+    // so one problem and a batch get the same bits by different routes
+    acc_add_from(acc, out, sd.dp);
     gemm_blocks<1>(acc, sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)r.k0 * TB, sd.dp, TB,
                    sd.gr + (int64_t)bj * TB * sd.dp + (int64_t)r.k0 * TB, sd.dp, TB, k1 - r.k0, st);
-    double* out = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)bj * TB;
-    double old[2][2][4];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int v = 0; v < 2; ++v)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) old[u][v][q] = out[(int64_t)acc_row(u, q) * sd.dp + acc_col(v)];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int v = 0; v < 2; ++v)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          out[(int64_t)acc_row(u, q) * sd.dp + acc_col(v)] = old[u][v][q] - acc.t[2 * u + v][q];
     if (bi == r.dg && bj == r.dg) {
       // no other work group of this launch reads this block (their operands
-      // are columns before k1 <= dg); its factorisation starts as soon as it
-      // is complete (written above, read back by the same work group)
+      // are columns before k1 <= dg): it goes to its factorisation in LDS
       __syncthreads();
-      diag_tile(sd, r.dg, f.flags, sm.d);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int i = acc_row(u, q), j = acc_col(v);
+            sm.d.Am[i][j] = j <= i ? acc.t[2 * u + v][q] : 0.0;
+            sm.d.Wm[i][j] = 0.0;
+          }
+      diag_core(f.flags, sm.d);
+      diag_store(sd, r.dg, sm.d);
+      return;
     }
+    acc_store(acc, out, sd.dp, 1.0);
   } else {
     b -= nq;
     const int ib = r.sa + b / (k1 - r.j0), jb = r.j0 + b % (k1 - r.j0);
@@ -1301,18 +1496,25 @@ __global__ __launch_bounds__(NT) void k_finalize(FacArgs f0, BatchCtx bc) {
   const int d = sd.d, dp = sd.dp;
   const int rs = d - TB - bj * TB, cs = d - TB - bi * TB;
   const int t = threadIdx.x;
-  for (int e = t; e < TB * TB; e += NT) {
-    const int x = e >> 6, y = e & 63, r = rs + x, c = cs + y;
-    S[x][y] = (r >= 0 && r < d && c >= 0 && c < d) ? sd.li[(int64_t)r * dp + c] : 0.0;
+  double v[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {  // every load issued first, from clamped addresses
+    const int e = t + NT * s, r = rs + (e >> 6), c = cs + (e & 63);
+    const bool ok = r >= 0 && c >= 0;  // (r, c < d always)
+    const double x = sd.li[ok ? (int64_t)r * dp + c : 0];
+    v[s] = ok ? x : 0.0;
   }
+#pragma unroll
+  for (int s = 0; s < 16; ++s) S[(t + NT * s) >> 6][t & 63] = v[s];
   if (t < TB) {
     const int r = rs + t;
     sc[t] = (r >= 0 && r < d) ? sd.gr[(int64_t)r * dp + r] : 1.0;
   }
   __syncthreads();
   const int orow = side == 0 ? bi : bj, ocol = side == 0 ? bj : bi;
-  for (int e = t; e < TB * TB; e += NT) {
-    const int a = e >> 6, b = e & 63;
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const int e = t + NT * s, a = e >> 6, b = e & 63;
     const int i = orow * TB + a, j = ocol * TB + b;
     double val;
     if (i >= d || j >= d || i == j) {
@@ -1330,11 +1532,6 @@ __global__ __launch_bounds__(NT) void k_finalize(FacArgs f0, BatchCtx bc) {
   }
 }
 
-__global__ void k_zero_flags_batch(const FacProb* tab, int count) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < count) tab[p].base->f.flags[0] = 0;
-}
-
 // Stream-ordered upload of up to PUT_WORDS 8-byte words that travel as
 // kernel arguments (no host buffer has to outlive the enqueueing call).
 constexpr int PUT_WORDS = 384;
@@ -1346,6 +1543,18 @@ struct PutArgs {
 __global__ void k_put(PutArgs p) {
   for (int i = threadIdx.x; i < p.n; i += blockDim.x) p.dst[i] = p.w[i];
 }
+
+// How the panels of one problem are grouped, by its block columns (us for the
+// whole factorisation, left-looking groups of four / right-looking groups of
+// four / one right-looking group of all panels):
+//   512 x 384: 238 / 218 / 208, 1000 x 700: 546 / 503 / 448, 1536: 996 / 972 / 877,
+//   2048: 1349 / 1312 / 1322, 3000 x 2000: 2420 / 2403 / 2413, 4096: 4255 / 4193 / -,
+//   8192 (groups of eight): 24143 / 25398 / -
+// Right-looking, each update on the chain is one product deep instead of up to
+// four; from some size on its extra tiles take the device from the far updates.
+// A batch fills the device and stays left-looking: fewer passes over memory.
+constexpr int kRightLooking = 64;
+constexpr int kOneGroup = 24;
 
 static gptq2d_status check_launch(const char* what);
 
@@ -1463,21 +1672,50 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     if (!tab) launch(std::false_type{}, dim3(per), BatchCtx{nullptr, 0}, st);
     else launch(std::true_type{}, dim3(per * count), BatchCtx{tab, per}, st);
   };
-  if (!tab) hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, f.flags, 1);
-  else hipLaunchKernelGGL(k_zero_flags_batch, dim3((count + 63) / 64), dim3(64), 0, s, tab, count);
-  // Gram: sides whose dimension is a multiple of 128 through the prepared
-  // panel and 128 x 128 tiles, the others with 64 x 64 tiles straight from
-  // the input
-  int fast = 0, slow = 0, nprep = 0, nslow = 0;
+  // (the Gram kernels clear the error flags: the diagonal blocks raise them)
+  if (nb0 == 1 && nb1 == 1) {
+    go(2, s, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
+      constexpr bool BT = decltype(bat)::value;
+      if (dt == GPTQ2D_F32)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_one_block<float, BT>), g, dim3(NT), 0, st, a, (const float*)A,
+                           lda, (const float*)B, ldb, bc);
+      else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_one_block<double, BT>), g, dim3(NT), 0, st, a,
+                           (const double*)A, lda, (const double*)B, ldb, bc);
+    });
+    return check_launch("factorisation launch");
+  }
+  // Gram: small sides on 32 x 32 tiles, larger ones whose dimension is a
+  // multiple of 128 through the prepared panel and 128 x 128 tiles, the others
+  // with 64 x 64 tiles straight from the input
+  const int fast = fast_sides(f.m, f.n);
+  // a batch whose 64 x 64 tiles fill the device by themselves takes those: half
+  // the loads per product, and the same sums in the same order (64 problems of
+  // 512 x 384: the call 2.05 instead of 2.14 ms)
+  const bool many = (int64_t)tri * (tab ? count : 1) >= 4 * (int64_t)f.cus;
+  int small = 0, slow = 0, nprep = 0, nslow = 0, nsmall = 0;
   for (int sd = 0; sd < 2; ++sd) {
     const int d = a.s[sd].d, nb = a.s[sd].nb;
-    if (d % 128 == 0) {
-      fast |= 1 << sd;
+    if (d <= kSmallGram && !many) {
+      small |= 1 << sd;
+      nsmall += nb * (2 * nb + 1);
+    } else if (fast & (1 << sd)) {
       nprep += (d / TB) * (d / TB);
     } else {
       slow |= 1 << sd;
       nslow += nb * (nb + 1) / 2;
     }
+  }
+  if (small) {
+    go(nsmall, s, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
+      constexpr bool BT = decltype(bat)::value;
+      if (dt == GPTQ2D_F32)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gram32<float, BT>), g, dim3(NT), 0, st, a, (const float*)A,
+                           lda, (const float*)B, ldb, small, bc);
+      else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gram32<double, BT>), g, dim3(NT), 0, st, a,
+                           (const double*)A, lda, (const double*)B, ldb, small, bc);
+    });
   }
   if (fast) {
     const GramPlan pl = gram_plan(f.m, f.n, fast, f.cus);
@@ -1563,7 +1801,8 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   // the next group's near update writes those columns and waits for that
   // part only, not for the rest behind it. Eight panels per group from 96
   // block columns on (measured faster at 8192), four below (at 4096).
-  const int GROUP = nbmax > 96 ? 8 : 4;
+  const bool right = !tab && nbmax <= kRightLooking;
+  const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
   hipError_t he = hipSuccess;
   bool far_pending = false, far1_pending = false;
   for (int g0 = 0; g0 < nbmax; g0 += GROUP) {
@@ -1586,7 +1825,12 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       // left-looking inside the group: the next panel's column of Q and row
       // of S get all of the group's finished panels at once (the later
       // columns wait for their own turn)
-      if (kb + 1 < g1) update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1}, s);
+      // right-looking: every later column of the group receives the panel just
+      // finished, one product deep
+      if (kb + 1 < g1) {
+        if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1}, s);
+        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1}, s);
+      }
     }
     if (far1_pending) {
       // the previous group's far update of the columns g1 .. g2-1 (and,
@@ -1683,7 +1927,7 @@ gptq2d_status launch_import(Factors& f, const double* L, int64_t ldl, const doub
                      f.n, f.np, f.U, 0);
   hipLaunchKernelGGL(k_import_lam, dim3((f.mp + bs - 1) / bs), dim3(bs), 0, s, lamL, f.m, f.mp, f.dL);
   hipLaunchKernelGGL(k_import_lam, dim3((f.np + bs - 1) / bs), dim3(bs), 0, s, lamU, f.n, f.np, f.dU);
-  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, f.flags, 1);
+  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, f.flags, 2);
   return check_launch("factor import");
 }
 

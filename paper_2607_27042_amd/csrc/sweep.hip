@@ -57,10 +57,12 @@ struct StageArgs {
   double* E;
   double* C;
   double* objp;
+  double* obj;        // the objective (nullable), summed by the last launch's tile
   int* flags;
   const int4* tasks;  // this launch's deliveries, grouped by bin
   const int4* bins;   // this launch's bins (one work group each)
   int stage, ilo, nsweep;
+  int set_flags;      // this launch sets the error word instead of adding to it
   // batched rounding: the problem's per-stage table {first task, first bin,
   // bins, 0}; tasks and bins then point at the problem's whole plan
   const int4* stab;
@@ -103,6 +105,7 @@ struct SweepSmem {
     Stage64 g;
   };
   double red[ST / 64];
+  int bad[ST / 64];
   int done[BANDS];  // per band: steps finished
   int prep[BANDS];  // per band: steps whose values in Xs and Ct are ready
 };
@@ -835,14 +838,45 @@ __device__ void run_sweep(const StageArgs& a, int I, int J, SweepSmem& sm) {
   __syncthreads();
   sweep_output<T>(a, sm, I, J, BR * (BANDS - 1) + BR / 8 * w, BR / 8, du, interior, part, bad);
 
-  if (bad) raise_flag(a.flags, bad);
+  bad = __any(bad & FLAG_NONFINITE) ? bad | FLAG_NONFINITE : bad;
+  bad = __any(bad & FLAG_OVERFLOW) ? bad | FLAG_OVERFLOW : bad;
+  bad = __any(bad & FLAG_TIMEOUT) ? bad | FLAG_TIMEOUT : bad;
+  auto wave_sum = [](double v) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off, 64);
-  if (l == 0) sm.red[w] = part;
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+  };
+  auto group_sum = [&]() {
+    return ((sm.red[0] + sm.red[1]) + (sm.red[2] + sm.red[3])) + ((sm.red[4] + sm.red[5]) + (sm.red[6] + sm.red[7]));
+  };
+  part = wave_sum(part);
+  if (l == 0) {
+    sm.red[w] = part;
+    sm.bad[w] = bad;
+  }
   __syncthreads();
-  if (t == 0)
-    a.objp[I * a.NT + J] = ((sm.red[0] + sm.red[1]) + (sm.red[2] + sm.red[3])) +
-                           ((sm.red[4] + sm.red[5]) + (sm.red[6] + sm.red[7]));
+  const double own = group_sum();
+  if (t == 0) {
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < ST / 64; ++i) any |= sm.bad[i];
+    // the first launch of a round has one tile, which sets the error word (a
+    // batch shares one word, cleared beforehand)
+    if (a.set_flags) a.flags[0] = any;
+    else if (any) raise_flag(a.flags, any);
+    a.objp[I * a.NT + J] = own;
+  }
+  // the last launch has one tile, too: every other tile's part is in memory
+  if (a.obj && I == a.MT - 1 && J == a.NT - 1) {
+    const int count = a.MT * a.NT - 1;
+    double s = 0.0;
+    for (int i = t; i < count; i += ST) s += a.objp[i];
+    s = wave_sum(s);
+    __syncthreads();
+    if (l == 0) sm.red[w] = s;
+    __syncthreads();
+    if (t == 0) a.obj[0] = group_sum() + own;
+  }
 }
 
 template <typename T>
@@ -878,6 +912,7 @@ struct BatchProb {
 struct BatchLaunch {
   const BatchProb* desc;
   int* flags;  // the batch's error word
+  double* obj; // the problems' objectives (nullable)
   int count, stage;
   int off[BATCH_MAX + 1];
 };
@@ -913,6 +948,7 @@ __global__ __launch_bounds__(ST) void k_stage_batch(BatchLaunch bl) {
     else hi = mid - 1;
   }
   StageArgs a = batch_args(bl.desc[lo], bl.flags);
+  a.obj = bl.obj ? bl.obj + lo : nullptr;
   const int k = bl.stage, lb = b - bl.off[lo];
   const int4 st = a.stab[k];
   a.stage = k;
@@ -927,41 +963,6 @@ __global__ __launch_bounds__(ST) void k_stage_batch(BatchLaunch bl) {
   } else {
     run_bin(a, a.bins[lb - a.nsweep], sm.t);
   }
-}
-
-// Objective of every problem of a batch: block p sums problem p's per-tile
-// partials in a fixed order.
-__global__ __launch_bounds__(NT) void k_obj_reduce_batch(const BatchProb* desc, double* out) {
-  __shared__ double red[NT];
-  const BatchProb& q = desc[blockIdx.x];
-  const int count = q.base->MT * q.base->NT;
-  const double* objp = carve_workspace(q.ws, q.base->mp, q.base->np, q.base->MT, q.base->NT).objp;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += NT) s += objp[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int i = 0; i < NT; ++i) tot += red[i];
-    out[blockIdx.x] = tot;
-  }
-}
-
-__global__ __launch_bounds__(NT) void k_obj_reduce(const double* part, int count, double* out) {
-  __shared__ double red[NT];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += NT) s += part[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int i = 0; i < NT; ++i) tot += red[i];
-    out[0] = tot;
-  }
-}
-
-__global__ void k_zero_flags(int* p) {
-  if (threadIdx.x == 0) p[0] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1121,7 +1122,7 @@ void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<
 // loaded with its duration (and stay empty when the work fits beside the
 // sweeps).
 // (least-squares fit of measured bin durations at 4096 and 8192)
-constexpr double kSweepCost = 45.0;   // one tile sweep
+constexpr double kSweepCost = 35.0;   // one tile sweep
 constexpr double kChunk4 = 5.1;       // 32-deep chunk onto 2 x 2 tiles
 constexpr double kChunk2 = 2.4;       // onto 2 x 1 or 1 x 2 tiles
 constexpr double kChunk1 = 1.2;       // onto one tile
@@ -1313,7 +1314,7 @@ static gptq2d_status round_typed(const Factors& f, const void* X, int64_t ldx, i
                                  int64_t ldz, void* Y, int64_t ldy, double* objective,
                                  const Workspace& ws, hipStream_t s, bool allow_timing) {
   StageArgs a = stage_args<T>(f, X, ldx, Z, ldz, Y, ldy, ws);
-  hipLaunchKernelGGL(k_zero_flags, dim3(1), dim3(64), 0, s, ws.flags);
+  a.obj = objective;
   const Schedule& S = f.sched;
   for (int k = 0; k < S.stages; ++k) {
     int ilo, ihi;
@@ -1321,6 +1322,7 @@ static gptq2d_status round_typed(const Factors& f, const void* X, int64_t ldx, i
     a.stage = k;
     a.ilo = ilo;
     a.nsweep = ihi - ilo + 1;
+    a.set_flags = k == 0;
     const int ntasks = S.bin_offset[k + 1] - S.bin_offset[k];  // work groups beside the sweeps
     a.tasks = S.d_tasks ? S.d_tasks + S.offset[k] : nullptr;
     a.bins = S.d_bins ? S.d_bins + S.bin_offset[k] : nullptr;
@@ -1340,8 +1342,6 @@ static gptq2d_status round_typed(const Factors& f, const void* X, int64_t ldx, i
     // the dispatch itself (no marker packets between the launches)
     hipExtLaunchKernelGGL(k_stage<T>, dim3(a.nsweep + ntasks), dim3(ST), 0, s, e0, e1, 0, a);
   }
-  if (objective)
-    hipLaunchKernelGGL(k_obj_reduce, dim3(1), dim3(NT), 0, s, ws.objp, f.MT * f.NT, objective);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "sweep launch");
   return GPTQ2D_OK;
@@ -1374,7 +1374,9 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
   int* flags = (int*)base;
   BatchProb* desc = (BatchProb*)(base + 256);
   char* region = base + 256 + batch_table_bytes(count);
-  std::vector<BatchProb> h(count);
+  // the table behind a cleared error word, in one upload
+  std::vector<char> head(256 + (size_t)count * sizeof(BatchProb), 0);
+  BatchProb* const h = reinterpret_cast<BatchProb*>(head.data() + 256);
   for (int p = 0; p < count; ++p) {
     const Workspace ws = workspace_carve(*f[p], region);
     // X, Z, Y as the problem's sweep addresses them (mirrored in reverse order)
@@ -1382,8 +1384,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
     h[p] = BatchProb{(const StageArgs*)f[p]->sched.d_base, a.X, a.Z, a.Y, a.ldx, a.ldz, a.ldy, a.cstep, region};
     region += align256(workspace_bytes(*f[p]));
   }
-  hipLaunchKernelGGL(k_zero_flags, dim3(1), dim3(64), 0, s, flags);
-  const gptq2d_status st = enqueue_upload(desc, h.data(), h.size() * sizeof(BatchProb), s);
+  const gptq2d_status st = enqueue_upload(base, head.data(), head.size(), s);
   if (st != GPTQ2D_OK) return st;
   for (int g0 = 0; g0 < count; g0 += BATCH_MAX) {
     const int cnt = std::min(BATCH_MAX, count - g0);
@@ -1392,6 +1393,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
     BatchLaunch bl;
     bl.desc = desc + g0;
     bl.flags = flags;
+    bl.obj = objective ? objective + g0 : nullptr;
     bl.count = cnt;
     for (int k = 0; k < smax; ++k) {
       int tot = 0;
@@ -1404,7 +1406,6 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
       hipLaunchKernelGGL(k_stage_batch<T>, dim3(tot), dim3(ST), 0, s, bl);
     }
   }
-  if (objective) hipLaunchKernelGGL(k_obj_reduce_batch, dim3(count), dim3(NT), 0, s, desc, objective);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "batched sweep launch");
   return GPTQ2D_OK;

@@ -1,0 +1,67 @@
+"""The factorisation's routes by size: one launch for one block per side, Grams
+on 32 x 32, 64 x 64 and 128 x 128 tiles, one group of panels or several,
+right-looking or left-looking. Factors against the oracle's explicit-inverse
+route (1e-10, the agreement of the two fp64 routes on these bases), and a
+batch large enough to take other routes than a single problem against the
+single problem: the same sums in the same order, hence the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import parity as pr
+from paper_2607_27042_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n", [(1, 64), (63, 64), (64, 65), (96, 1), (1024, 31), (1025, 33), (1152, 127), (1600, 66)])
+@pytest.mark.parametrize("reverse", [False, True])
+def test_routes_match_oracle(m, n, reverse):
+    p = wl.random_problem(m, n, 41, "f64", "general")
+    X, A, B = p.widened()
+    f = binding.Factors.from_bases(pr.to_dev(p.A), pr.to_dev(p.B), reverse=reverse)
+    L, U, lamL, lamU = (t.cpu().numpy() for t in f.export())
+    f.close()
+    if reverse:
+        A, B = np.ascontiguousarray(A[:, ::-1]), np.ascontiguousarray(B[::-1])
+    Lo, lamLo, Uo, lamUo = oracle.factors(A, B)
+    for got, ref in ((L, Lo), (U, Uo)):
+        assert np.abs(got - ref).max() <= 1e-10 * max(1.0, np.abs(ref).max())
+    np.testing.assert_allclose(lamL, lamLo, rtol=1e-10)
+    np.testing.assert_allclose(lamU, lamUo, rtol=1e-10)
+
+
+@pytest.mark.parametrize("m,n,count", [(512, 384, 18), (130, 70, 160), (64, 40, 300), (1152, 64, 2)])
+def test_batch_routes_same_bits(m, n, count):
+    g = torch.Generator(device="cuda").manual_seed(7)
+
+    def basis(d):
+        t = torch.randn(d, d, generator=g, device="cuda", dtype=torch.float64) / d ** 0.5
+        t.diagonal().add_(2.0)
+        return t
+    As, Bs = [basis(m) for _ in range(count)], [basis(n) for _ in range(count)]
+    fs = [binding.Factors(m, n) for _ in range(count)]
+    binding.factor_batched(fs, As, Bs)
+    one = binding.Factors(m, n)
+    for p in (0, count // 2, count - 1):
+        one.compute(As[p], Bs[p])
+        for x, y in zip(one.export(), fs[p].export()):
+            assert torch.equal(x, y), f"problem {p}"
+
+
+@pytest.mark.parametrize("side", ["A", "B"])
+@pytest.mark.parametrize("m,n", [(20, 64), (64, 96)])
+def test_singular_side_is_reported(side, m, n):
+    """Each side's error word is read, and cleared by the next factorisation."""
+    A = torch.eye(m, device="cuda", dtype=torch.float64)
+    B = torch.eye(n, device="cuda", dtype=torch.float64)
+    bad = {"A": A.clone(), "B": B.clone()}
+    bad[side][0, 0] = 0.0
+    f = binding.Factors(m, n)
+    f.compute(bad["A"], bad["B"])
+    with pytest.raises(binding.Gptq2dError) as e:
+        binding.gptq2d_factor_check(f.handle)
+    assert e.value.status == -2  # GPTQ2D_ERR_SINGULAR
+    f.compute(A, B)
+    binding.gptq2d_factor_check(f.handle)
