@@ -78,10 +78,14 @@ constexpr int BANDS = ST / 128;    // bands, each with a pair of waves
 constexpr int BANDB = NB / BANDS;  // block rows of a band
 constexpr int STEPS = NB + BANDB - 1;
 constexpr int PAD = BS * (BANDB - 1);
-constexpr int TE = TB + PAD;       // LDS row stride of the tile arrays (doubles)
+// LDS row strides (doubles), at least TB + PAD. LDS serves 16 lanes of a 64-bit
+// access at a time (4.2 cycles per wave instruction without conflicts): 76 has
+// none in either layout of Et and Xs and for U's blocks, 80 takes 16 cycles for
+// the chain layout; the transposed accesses of Ct take 8 at 78, 16 at 76 or 80.
+constexpr int TE = TB + PAD;       // Et, Xs and Us
+constexpr int TC = TE + 2;         // Ct
 constexpr int TEN = TB * TE + PAD;
-constexpr int TX = TB + 4 * BS;    // of Et and Xs: rows of four blocks of 32 lanes hit 64 different banks
-constexpr int TXN = TB * TX + 4 * BS;
+constexpr int TCN = TB * TC + PAD;
 
 // LDS of a sweeping work group. A row of the arrays starts with 12 columns of
 // zeros (the row before ends in them): a bank whose block column is still to
@@ -95,12 +99,12 @@ constexpr int TXN = TB * TX + 4 * BS;
 //     outside the tile and meets a zero; like everything here it is finite.
 // Before the sweep the bytes of Et and Xs stage the two neighbour products.
 struct SweepSmem {
-  double Ct[TEN];
+  double Ct[TCN];
   double Us[TB * TE];
   union {
     struct {
-      double Et[TXN];
-      double Xs[TXN];
+      double Et[TEN];
+      double Xs[TEN];
     };
     Stage64 g;
   };
@@ -495,50 +499,62 @@ __device__ __forceinline__ void sweep_band(const double* Ltile, SweepSmem& sm, i
   const int mrow = BS * (BANDB * W + b);
   lds_double* pu = (lds_double*)(sm.Us + (r - BS * b) * TE + c - BS * b);  // block (J, J) of U
   lds_double* pw = (lds_double*)(sm.Us - BS * r * TE + c - BS * r);        // the same, chain layout
-  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TE + r - BS * b);  // Ct, transposed
+  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TC + r - BS * b);  // Ct, transposed
   // Et, matrix layout, two block rows up (their weights are zero where the
   // band has none); Xs is at a constant distance
-  lds_double* pe = (lds_double*)(sm.Et + PAD + (mrow - 2 * BS + r) * TX + c - BS * b);
-  lds_double* po = (lds_double*)(sm.Et + PAD + (cr + b) * TX + c - BS * r);    // Et, chain layout
-  constexpr int EX = TXN;  // from Et to Xs
+  lds_double* pe = (lds_double*)(sm.Et + PAD + (mrow - 2 * BS + r) * TE + c - BS * b);
+  lds_double* po = (lds_double*)(sm.Et + PAD + (cr + b) * TE + c - BS * r);    // Et, chain layout
+  constexpr int EX = TEN;  // from Et to Xs
 
   int seen = 0;
   wait_count(&sm.prep[W], 1, seen, bad);
   double dt = pt[0], ct = 0.0, u2 = 0.0;
-  pe[EX + 2 * BS * TX] = mfma4(dt, pu[0], pe[EX + 2 * BS * TX]);
+  pe[EX + 2 * BS * TE] = mfma4(dt, pu[0], pe[EX + 2 * BS * TE]);
   asm volatile("" ::: "memory");
   double y = po[EX], err;
+  double uw[BS];
+#pragma unroll
+  for (int k = 0; k < BS; ++k) uw[k] = pw[k * TE];
 #pragma unroll 1
   for (int s = 0; s < STEPS; ++s) {
     // (opaque addresses: constant offsets from them fit the LDS instructions)
     asm volatile("" : "+v"(pu), "+v"(pw), "+v"(pt), "+v"(pe), "+v"(po));
     // operands of the next step, read while this one's chain runs; if its
     // values were not ready yet they are read again behind it
-    double uw[BS];
-#pragma unroll
-    for (int k = 0; k < BS; ++k) uw[k] = pw[k * TE];
     seen = load_count(&sm.prep[W]);
     asm volatile("" ::: "memory");
-    double xn = pe[EX + 2 * BS * TX + BS], dn = pt[BS];
+    double xn = pe[EX + 2 * BS * TE + BS], dn = pt[BS];
     const double e2 = pe[BS], u1 = pu[BS], un = pu[BS * TE + BS], u2n = pu[2 * BS];
     block_chain(y, err, lw, uw, self);
     po[0] = err;
-    po[EX] = y;
     asm volatile("" ::: "memory");
-    const double em = pe[2 * BS * TX], e1 = pe[BS * TX + BS];
+    const double em = pe[2 * BS * TE], e1 = pe[BS * TE + BS];
+    po[EX] = y;
+#pragma unroll
+    for (int k = 0; k < BS; ++k) uw[k] = pw[BS * TE + BS + k * TE];
+    double xa = mfma4(ct, u2, xn), da = mfma4(e2, la2, dn);
     if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) < min(s + 2, STEPS), 0)) {
-      wait_count(&sm.prep[W], min(s + 2, STEPS), seen, bad);
-      xn = pe[EX + 2 * BS * TX + BS];
-      dn = pt[BS];
+      // (counter before values: the values are valid if the counter was)
+      int spins = 0;
+      do {
+        seen = load_count(&sm.prep[W]);
+        asm volatile("" ::: "memory");
+        xn = pe[EX + 2 * BS * TE + BS];
+        dn = pt[BS];
+        if (++spins > (1 << 22)) {
+          bad |= FLAG_TIMEOUT;
+          break;
+        }
+      } while (__builtin_amdgcn_readfirstlane(seen) < min(s + 2, STEPS));
+      xa = mfma4(ct, u2, xn);
+      da = mfma4(e2, la2, dn);
     }
-    xn = mfma4(ct, u2, xn);
-    dn = mfma4(e2, la2, dn);
     ct = mfma4(em, la0, dt);
-    dt = mfma4(e1, la1, dn);
-    double ym = mfma4(ct, u1, xn);
+    dt = mfma4(e1, la1, da);
+    double ym = mfma4(ct, u1, xa);
     ym = mfma4(dt, un, ym);
     pt[0] = ct;
-    pe[EX + 2 * BS * TX + BS] = ym;
+    if (s + 1 < STEPS) pe[EX + 2 * BS * TE + BS] = ym;  // (a column further is the next row's first)
     asm volatile("" ::: "memory");
     y = po[EX + BS];
     store_count(&sm.done[W], s + 1);
@@ -570,10 +586,10 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
 
   // LDS addresses of step 0
   lds_double* pu = (lds_double*)(sm.Us + (r - BS * b - 3 * BS) * TE + c - BS * b);  // block (J - 3, J) of U
-  lds_double* pm = (lds_double*)(sm.Xs + PAD + (mrow + r) * TX + c - BS * b);
-  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TE + r - BS * b);
-  lds_double* pe = (lds_double*)(sm.Et + PAD + r * TX + c - BS * b);
-  lds_double* p3 = (lds_double*)(sm.Et + PAD + (mrow - 3 * BS + r) * TX + c - BS * b);
+  lds_double* pm = (lds_double*)(sm.Xs + PAD + (mrow + r) * TE + c - BS * b);
+  lds_double* pt = (lds_double*)(sm.Ct + PAD + (mrow + c) * TC + r - BS * b);
+  lds_double* pe = (lds_double*)(sm.Et + PAD + r * TE + c - BS * b);
+  lds_double* p3 = (lds_double*)(sm.Et + PAD + (mrow - 3 * BS + r) * TE + c - BS * b);
 
   constexpr int ND = NB - 3;
   double acc[ND + 1], uv[ND], ev[NQ > 0 ? NQ : 1];
@@ -591,7 +607,7 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
     d0 = pt[at];
     d1 = 0.0;
 #pragma unroll
-    for (int q = 0; q < NO; ++q) ev[q] = pe[BS * q * TX + at];
+    for (int q = 0; q < NO; ++q) ev[q] = pe[BS * q * TE + at];
   };
   auto far = [&]() {
 #pragma unroll
@@ -607,7 +623,7 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
     begin(0);
     if (W > 0) wait_count(up, k + BANDB, above, bad);
 #pragma unroll
-    for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TX];
+    for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TE];
     far();
     near();
     if (W > 0) *pt = d0 + d1;
@@ -619,21 +635,31 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
     p3 += BS;
   }
   begin(0);
-#pragma unroll
-  for (int d = 0; d < ND; ++d) uv[d] = pu[BS * d];
+  uv[0] = pu[0];
   far();
 #pragma unroll 1
   for (int k = 3; k < STEPS; ++k) {
     asm volatile("" : "+v"(pu), "+v"(pm), "+v"(pt), "+v"(pe), "+v"(p3));
-    if (W > 0) {
-      if (__builtin_expect(__builtin_amdgcn_readfirstlane(above) < min(k + BANDB, STEPS), 0))
-        wait_count(up, min(k + BANDB, STEPS), above, bad);
-    }
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane(seen) < k - 2, 0)) wait_count(&sm.done[W], k - 2, seen, bad);
-    asm volatile("" ::: "memory");
-    const double ct = pt[-3 * BS], e3 = *p3;
+    // counters before values: the values are valid if the counters were
+    double ct, e3;
+    for (int spins = 0;;) {
+      seen = load_count(&sm.done[W]);
+      if (W > 0) above = load_count(up);
+      asm volatile("" ::: "memory");
+      ct = pt[-3 * BS];
+      e3 = *p3;
 #pragma unroll
-    for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TX];
+      for (int q = NO; q < NQ; ++q) ev[q] = pe[BS * q * TE];
+      const bool there = __builtin_amdgcn_readfirstlane(seen) >= k - 2 &&
+                         (W == 0 || __builtin_amdgcn_readfirstlane(above) >= min(k + BANDB, STEPS));
+      if (__builtin_expect(there, 1)) break;
+      if (++spins > (1 << 22)) {
+        bad |= FLAG_TIMEOUT;
+        break;
+      }
+    }
+#pragma unroll
+    for (int d = 1; d < ND; ++d) uv[d] = pu[BS * d];
     __builtin_amdgcn_sched_barrier(0);
     acc[0] = mfma4(ct, uv[0], acc[1]);
     d1 = mfma4(e3, la3, d1);
@@ -644,9 +670,6 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
     // the next step's operands
     begin(BS);
     uv[0] = pu[BS * TE + BS];
-    seen = load_count(&sm.done[W]);
-    if (W > 0) above = load_count(up);
-    asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     // the feedback on the steps further ahead; blocks past the tile's last
     // column are left out
@@ -654,10 +677,7 @@ __device__ __forceinline__ void prepare_band(const double* Ltile, SweepSmem& sm,
     for (int c0 = 1; c0 < ND; c0 += 4) {
       if (k + c0 < STEPS) {
 #pragma unroll
-        for (int d = c0; d < c0 + 4 && d < ND; ++d) {
-          acc[d] = mfma4(ct, uv[d], acc[d + 1]);
-          uv[d] = pu[BS * TE + BS + BS * d];
-        }
+        for (int d = c0; d < c0 + 4 && d < ND; ++d) acc[d] = mfma4(ct, uv[d], acc[d + 1]);
       }
     }
     far();
@@ -683,10 +703,10 @@ __device__ __forceinline__ void sweep_output(const StageArgs& a, const SweepSmem
   for (int i = 0; i < n; ++i) {
     const int rr = r0 + i;
     const int64_t gi = (int64_t)I * TB + rr;
-    const int at = PAD + rr * TX + l;
+    const int at = PAD + rr * TE + l;
     const double y = sm.Xs[at], e = sm.Et[at];
     E[r_idx(rr, l)] = e;
-    C[s_idx(rr, l)] = sm.Ct[PAD + rr * TE + l];
+    C[s_idx(rr, l)] = sm.Ct[PAD + rr * TC + l];
     if (interior || (in && gi < a.m)) {
       // (a NaN fails the range test, too)
       if (!(y >= -2147483648.5 && y < 2147483647.5)) bad |= isfinite(y) ? FLAG_OVERFLOW : FLAG_NONFINITE;
@@ -797,14 +817,15 @@ __device__ void run_sweep(const StageArgs& a, int I, int J, SweepSmem& sm) {
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      sm.Xs[PAD + (ar + 16 * u + 4 * q) * TX + ac] = accR[u][q];
-      sm.Ct[PAD + (ar + 16 * u + 4 * q) * TE + ac] = accD[u][q];
+      sm.Xs[PAD + (ar + 16 * u + 4 * q) * TE + ac] = accR[u][q];
+      sm.Ct[PAD + (ar + 16 * u + 4 * q) * TC + ac] = accD[u][q];
     }
   // the zero columns; no errors yet (a product with a zero weight must not meet
   // a NaN in memory that nobody has written)
-  for (int e = t; e < (TB + 1) * PAD; e += ST) sm.Ct[(e / PAD) * TE + e % PAD] = 0.0;
-  for (int e = t; e < (TB + 1) * 16; e += ST) sm.Xs[e < 12 ? e : (e / 16) * TX + e % 16 - (TX - TB - PAD)] = 0.0;
-  for (int e = t; e < TXN / 2; e += ST) *reinterpret_cast<double2*>(&sm.Et[2 * e]) = double2{0.0, 0.0};
+  for (int e = t; e < (TB + 1) * PAD; e += ST) sm.Xs[(e / PAD) * TE + e % PAD] = 0.0;
+  for (int e = t; e < PAD + TB * (TC - TB); e += ST)
+    sm.Ct[e < PAD ? e : PAD + TB + (e - PAD) / (TC - TB) * TC + (e - PAD) % (TC - TB)] = 0.0;
+  for (int e = t; e < TEN / 2; e += ST) *reinterpret_cast<double2*>(&sm.Et[2 * e]) = double2{0.0, 0.0};
   __syncthreads();
 
   double part = 0.0;
@@ -1058,9 +1079,13 @@ void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<
     }
   }
   // room per launch beside its sweeps: the idle compute units for the
-  // duration of one tile sweep, in 64^3-product units (about 16 per unit
-  // and sweep on a 256-unit device; only the ratio between launches and the
-  // total matter for the placement)
+  // duration of one tile sweep, in 64^3-product units (only the ratio between
+  // launches and the total matter for the placement). Measured rounds in ms at
+  // 12 / 16 / 20 units: 4096 x 4096 5.59 / 5.39 / 6.25, 4096 x 11008 20.3 / 19.7 /
+  // 18.9, 8192 x 8192 30.0 / 29.3 / 28.8: with more than 64 tiles on a side the
+  // middle launches are bound by the deliveries that are due there, and the
+  // early ones take more of them.
+  const double per_unit = std::max(MT, NTt) > 64 ? 20.0 : 16.0;
   std::vector<std::vector<int>> released(S);
   for (int i = 0; i < (int)batches.size(); ++i) released[batches[i].release].push_back(i);
   auto later = [&](int x, int y) {
@@ -1071,7 +1096,7 @@ void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<
   for (int k = 0; k < S; ++k) {
     for (int i : released[k]) avail.push(i);
     const int nsweep = std::min(k, MT - 1) - std::max(0, k - NTt + 1) + 1;
-    const double room = 16.0 * std::max(0, 256 - nsweep);
+    const double room = per_unit * std::max(0, 256 - nsweep);
     std::vector<int> held;
     while (!avail.empty()) {
       const int i = avail.top();
