@@ -146,8 +146,11 @@ __device__ __forceinline__ void gram_load(const T* S, int64_t ld, int d, int i0,
   for (int s = 0; s < 16; ++s) r[s] = ok[s] ? (double)v[s] : 0.0;
 }
 
+// A k-block in which one operand is all zeros (a triangular basis: two thirds of
+// them) adds nothing and is skipped; a NaN is not a zero.
 template <typename T, int SIDE>
 __device__ void gram_tile(const Side& sd, const T* S, int64_t ld, int bp, int bq, Stage64& st, int rev) {
+  __shared__ int vote[2][NT / 64];
   Acc acc;
   acc.zero();
   double ra[16], rb[16];
@@ -155,6 +158,14 @@ __device__ void gram_tile(const Side& sd, const T* S, int64_t ld, int bp, int bq
   gram_load<T, SIDE>(S, ld, sd.d, bq * TB, 0, rb, rev);
   const int nk = (sd.d + TB - 1) / TB;
   for (int kb = 0; kb < nk; ++kb) {
+    bool za = true, zb = true;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      za &= ra[s] == 0.0;
+      zb &= rb[s] == 0.0;
+    }
+    const int mine = (__all(za) ? 0 : 1) | (__all(zb) ? 0 : 2);
+    if ((threadIdx.x & 63) == 0) vote[kb & 1][threadIdx.x >> 6] = mine;
     if (SIDE == 0) {
       put_ak(st, ra);
       put_b(st, rb);
@@ -163,11 +174,12 @@ __device__ void gram_tile(const Side& sd, const T* S, int64_t ld, int bp, int bq
       put_bt(st, rb);
     }
     __syncthreads();
+    const int any = vote[kb & 1][0] | vote[kb & 1][1] | vote[kb & 1][2] | vote[kb & 1][3];
     if (kb + 1 < nk) {  // next block's loads in flight during this block's MFMAs
       gram_load<T, SIDE>(S, ld, sd.d, bp * TB, (kb + 1) * TB, ra, rev);
       gram_load<T, SIDE>(S, ld, sd.d, bq * TB, (kb + 1) * TB, rb, rev);
     }
-    mma_blk(acc, st);
+    if (any == 3) mma_blk(acc, st);
     __syncthreads();
   }
 #pragma unroll
@@ -310,10 +322,10 @@ __global__ __launch_bounds__(NT) void k_gram32(FacArgs f0, const T* A0, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Gram of a side whose dimension is a multiple of 128, in two steps.
+// Gram of a larger side, in two steps.
 //
-// k_gram_prep writes, widened to fp64, the row-major panel S (d x d, row
-// stride d) whose rows are the reversed Gram indices: S[p][k] = A[k][d-1-p]
+// k_gram_prep writes, widened to fp64, the row-major panel S (dp x dp, zeros
+// past d) whose rows are the reversed Gram indices: S[p][k] = A[k][d-1-p]
 // (side 0, a transpose through LDS) or B[d-1-p][k] (side 1); in reverse order
 // the problem is already the index-reversed one, S[p][k] = A[k][p] or B[p][k].
 // The panel lives in the side's inverse buffer, which the factorisation fills
@@ -353,6 +365,7 @@ __global__ __launch_bounds__(NT) void k_gram32(FacArgs f0, const T* A0, int64_t 
 struct GramPlan {
   int t0, t1;          // tiles of side 0 and side 1 on this path
   int n0, n1;          // 128-row blocks of side 0 and side 1 on this path
+  int b0, b1;          // their 64-wide blocks (an odd count: the last row block is half)
   int nch0, nch1;      // dense chunks per tile on each side
   int64_t units;       // dense units: t0 nch0 + t1 nch1
   int G;               // launch grid (work groups, an upper bound for the ranges)
@@ -420,13 +433,13 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
   const T* A = BAT ? (const T*)pb->A : A0;
   const T* B = BAT ? (const T*)pb->B : B0;
   const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
-  const int n0 = (sides & 1) ? (f.s[0].d / TB) * (f.s[0].d / TB) : 0;
+  const int n0 = (sides & 1) ? f.s[0].nb * f.s[0].nb : 0;
   int b = bat_block<BAT>(bc);
   if (b == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
   const int side = b < n0 ? 0 : 1;
   if (side == 1) b -= n0;
   const Side& sd = f.s[side];
-  const int d = sd.d, nt = d / TB;
+  const int d = sd.d, dp = sd.dp, nt = sd.nb;
   const int i0 = (b / nt) * TB, k0 = (b % nt) * TB;  // S rows i0.., columns k0..
   double* S = sd.li;
   const int t = threadIdx.x;
@@ -435,11 +448,14 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
   if (side == 0) {
     // A rows k0 + r, columns d-1-(i0+63) .. d-1-i0 (ascending; in reverse
     // order i0 .. i0+63), coalesced
+    // (c0 < 0 or past the end: the padding, zeros)
     const int c0 = rev ? i0 : d - i0 - TB;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int e = t + NT * u, r = e >> 6, c = e & 63;  // c: column offset in A
-      const double x = (double)A[(int64_t)(k0 + r) * lda + c0 + c];
+      const bool ok = k0 + r < d && c0 + c >= 0 && c0 + c < d;
+      const T y = A[ok ? (int64_t)(k0 + r) * lda + c0 + c : 0];
+      const double x = ok ? (double)y : 0.0;
       tile[r][c] = x;
       nz |= x != 0.0;
     }
@@ -448,15 +464,17 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int e = t + NT * u, i = e >> 6, k = e & 63;
-      S[(int64_t)(i0 + i) * d + k0 + k] = tile[k][rev ? i : TB - 1 - i];
+      S[(int64_t)(i0 + i) * dp + k0 + k] = tile[k][rev ? i : TB - 1 - i];
     }
   } else {
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int e = t + NT * u, i = e >> 6, k = e & 63;
       const int row = rev ? i0 + i : d - 1 - (i0 + i);
-      const double x = (double)B[(int64_t)row * ldb + k0 + k];
-      S[(int64_t)(i0 + i) * d + k0 + k] = x;
+      const bool ok = row >= 0 && row < d && k0 + k < d;
+      const T y = B[ok ? (int64_t)row * ldb + k0 + k : 0];
+      const double x = ok ? (double)y : 0.0;
+      S[(int64_t)(i0 + i) * dp + k0 + k] = x;
       nz |= x != 0.0;
     }
   }
@@ -470,7 +488,9 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
 }
 
 // (i0, i1 select the part i0 <= i < i1 of the loads)
-__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int c,
+// rp, rq: the rows the two panels have (64 in the last, half row block: its
+// other loads repeat a valid row and are not used)
+__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int rp, int rq, int c,
                                            GramChunk& g, int w, int l, int i0 = 0, int i1 = 8) {
   typedef __attribute__((address_space(3))) void lds_v;
   const int ar = l >> 4, ap = (l & 15) ^ ar;
@@ -478,9 +498,9 @@ __device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, i
 #pragma unroll
   for (int i = i0; i < i1; ++i) {
     const int j = w + 4 * i;
-    const int64_t ro = (int64_t)(4 * j + ar) * ld + k0;
-    __builtin_amdgcn_global_load_lds((const void*)(Sp + ro), (lds_v*)&g.a[j][0], 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((const void*)(Sq + ro), (lds_v*)&g.b[j][0], 16, 0, 0);
+    const int row = 4 * j + ar;
+    __builtin_amdgcn_global_load_lds((const void*)(Sp + (int64_t)min(row, rp - 1) * ld + k0), (lds_v*)&g.a[j][0], 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(Sq + (int64_t)min(row, rq - 1) * ld + k0), (lds_v*)&g.b[j][0], 16, 0, 0);
   }
 }
 
@@ -506,7 +526,7 @@ __global__ __launch_bounds__(PLT) void k_gram_plan(FacArgs f0, GramPlan pl, Batc
   }
   __syncthreads();
   for (int side = 0; side < 2; ++side) {
-    const int nk = 2 * (side ? pl.n1 : pl.n0);  // 64 x 64 blocks per panel row and column
+    const int nk = side ? pl.b1 : pl.b0;  // 64 x 64 blocks per panel row and column
     const int4* votes = (const int4*)v.mask[side];
     for (int e = t; e < nk * nk; e += PLT) {
       const int4 q = votes[e];
@@ -564,7 +584,7 @@ __global__ __launch_bounds__(PLT) void k_gram_plan(FacArgs f0, GramPlan pl, Batc
 // Chunks c0 .. c1-1 of the tile (bp, bq) of one side into acc (zeroed here).
 __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0, int c1, GramChunk* buf,
                                           d4 (&acc)[4][4]) {
-  const int d = sd.d;
+  const int d = sd.dp, rp = min(128, d - 128 * bp), rq = min(128, d - 128 * bq);
   const double* Sp = sd.li + (int64_t)(128 * bp) * d;
   const double* Sq = sd.li + (int64_t)(128 * bq) * d;
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
@@ -573,7 +593,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  if (c0 < c1) gram_issue(Sp, Sq, d, c0, buf[0], w, l);
+  if (c0 < c1) gram_issue(Sp, Sq, d, rp, rq, c0, buf[0], w, l);
   for (int c = c0; c < c1; ++c) {
     const int cb = (c - c0) & 1;
     // the next chunk's loads in two halves, the second half-way through this
@@ -581,7 +601,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
     // pipeline takes it)
     const bool more = c + 1 < c1;
     if (more) {
-      gram_issue(Sp, Sq, d, c + 1, buf[cb ^ 1], w, l, 0, 4);
+      gram_issue(Sp, Sq, d, rp, rq, c + 1, buf[cb ^ 1], w, l, 0, 4);
       __builtin_amdgcn_s_waitcnt(0x0f78);  // vmcnt(8): chunk c has landed
     } else {
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -603,7 +623,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
       const int cur = kk & 1, nx = cur ^ 1;
       if (kk == GQ / 8 && more) {
         __builtin_amdgcn_sched_barrier(0);
-        gram_issue(Sp, Sq, d, c + 1, buf[cb ^ 1], w, l, 4, 8);
+        gram_issue(Sp, Sq, d, rp, rq, c + 1, buf[cb ^ 1], w, l, 4, 8);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (kk + 1 < GQ / 4) {
@@ -634,13 +654,18 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
 __device__ __forceinline__ void gram_store(const Side& sd, int bp, int bq, const d4 (&acc)[4][4]) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, qr = w >> 1, qc = w & 1;
   if (bp == bq && qr < qc) return;
+  if (2 * bp + qr >= sd.nb || 2 * bq + qc >= sd.nb) return;  // past the last block
   double* o = sd.gr + (int64_t)(128 * bp + 64 * qr + (l >> 4)) * sd.dp + 128 * bq + 64 * qc + (l & 15);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o[(int64_t)(16 * i + 4 * r) * sd.dp + 16 * j] = acc[i][j][r];
+      for (int r = 0; r < 4; ++r) {
+        const int pp = 128 * bp + 64 * qr + 16 * i + 4 * r + (l >> 4), qq = 128 * bq + 64 * qc + 16 * j + (l & 15);
+        // (identity on the padding)
+        o[(int64_t)(16 * i + 4 * r) * sd.dp + 16 * j] = pp < sd.d && qq < sd.d ? acc[i][j][r] : pp == qq ? 1.0 : 0.0;
+      }
 }
 
 // Scratch slot of a partial product: every thread keeps its 64 values in
@@ -732,13 +757,14 @@ __global__ __launch_bounds__(NT) void k_gram_fix(FacArgs f0, GramPlan pl, const 
 
 static GramPlan gram_plan(int m, int n, int fast, int cus) {
   GramPlan pl;
-  const int n0 = m / 128, n1 = n / 128;
-  pl.n0 = (fast & 1) ? n0 : 0;
-  pl.n1 = (fast & 2) ? n1 : 0;
+  pl.b0 = (fast & 1) ? (m + TB - 1) / TB : 0;
+  pl.b1 = (fast & 2) ? (n + TB - 1) / TB : 0;
+  pl.n0 = (pl.b0 + 1) / 2;
+  pl.n1 = (pl.b1 + 1) / 2;
   pl.t0 = pl.n0 * (pl.n0 + 1) / 2;
   pl.t1 = pl.n1 * (pl.n1 + 1) / 2;
-  pl.nch0 = std::max(1, m / GQ);
-  pl.nch1 = std::max(1, n / GQ);
+  pl.nch0 = std::max(1, pl.b0 * (TB / GQ));
+  pl.nch1 = std::max(1, pl.b1 * (TB / GQ));
   pl.units = (int64_t)pl.t0 * pl.nch0 + (int64_t)pl.t1 * pl.nch1;
   const int64_t nmax = std::max(pl.t0 ? pl.nch0 : 1, pl.t1 ? pl.nch1 : 1);
   // every range at least one dense tile long: a tile meets at most one boundary
@@ -752,7 +778,7 @@ static GramPlan gram_plan(int m, int n, int fast, int cus) {
 constexpr int kSmallGram = 1024;
 
 static int fast_sides(int m, int n) {
-  return (m > kSmallGram && m % 128 == 0 ? 1 : 0) | (n > kSmallGram && n % 128 == 0 ? 2 : 0);
+  return (m > kSmallGram ? 1 : 0) | (n > kSmallGram ? 2 : 0);
 }
 
 size_t gram_part_doubles(int m, int n, int cus) {
@@ -1685,9 +1711,9 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     });
     return check_launch("factorisation launch");
   }
-  // Gram: small sides on 32 x 32 tiles, larger ones whose dimension is a
-  // multiple of 128 through the prepared panel and 128 x 128 tiles, the others
-  // with 64 x 64 tiles straight from the input
+  // Gram: small sides on 32 x 32 tiles (in a batch that fills the device, on
+  // 64 x 64 tiles) straight from the input, larger ones through the prepared
+  // panel and 128 x 128 tiles
   const int fast = fast_sides(f.m, f.n);
   // a batch whose 64 x 64 tiles fill the device by themselves takes those: half
   // the loads per product, and the same sums in the same order (64 problems of
@@ -1700,7 +1726,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       small |= 1 << sd;
       nsmall += nb * (2 * nb + 1);
     } else if (fast & (1 << sd)) {
-      nprep += (d / TB) * (d / TB);
+      nprep += nb * nb;
     } else {
       slow |= 1 << sd;
       nslow += nb * (nb + 1) / 2;
