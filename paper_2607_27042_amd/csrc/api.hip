@@ -42,6 +42,7 @@ static void free_all(Factors* f) {
   f->ev_near = f->ev_far = f->ev_far1 = f->ev_own = nullptr;
   f->aux = f->own = nullptr;
   free_schedule(f->sched);
+  if (!f->bshared) free_schedule(f->bsched);
 }
 
 static gptq2d_status alloc(Factors* f, void** p, size_t bytes) {
@@ -160,10 +161,28 @@ gptq2d_status gptq2d_factors_create(int m, int n, gptq2d_factors_t* out) {
   }
   if (st == GPTQ2D_OK) {
     // far-delivery batch width in source tiles: wider batches mean fewer
-    // read-modify-writes of the feedback buffers but coarser products; five
-    // measured best from about 128 tiles per side on, four below
-    const int g = std::max(f->MT, f->NT) > 64 ? 5 : 4;
-    st = build_schedule(*f, env_int("GPTQ2D_BATCH", g));
+    // read-modify-writes of the feedback buffers but longer products, and a
+    // launch lasts at least as long as its longest one. While the deliveries
+    // leave compute units idle (a launch has about MT NT / 2 products of 64^3)
+    // narrow ones win. Rounds in us at widths 2 / 3 / 4 / 5: 1000 x 700 (88 per
+    // launch) 718 / 750 / 822 / 956, 2048 x 2048 (512) 1853 / 1975 / 2178 / 2709,
+    // 3000 x 2000 (752) 2570 / 2531 / 2787 / 3529, 1024 x 8192 (1024) 5082 / 4808 /
+    // 5278 / 6786, 4096 x 4096 (2048) 5754 / 6083 / 5339 / 6299; five from about 128
+    // tiles a side on
+    const int per_launch = f->MT * f->NT / 2;
+    // A batch fills the device, so there the fewer passes count at any size (64
+    // problems of 512 x 384: 1.91 ms at four, 1.99 at two). The sums come in the
+    // order of the sources either way: the same bits.
+    const int wide = std::max(f->MT, f->NT) > 64 ? 5 : 4;
+    const int g = per_launch <= 640 ? 2 : per_launch <= 1280 ? 3 : wide;
+    const int gs = env_int("GPTQ2D_BATCH", g), gb = env_int("GPTQ2D_BATCH", wide);
+    st = build_schedule(*f, gs, f->sched);
+    if (st == GPTQ2D_OK && gb == gs) {
+      f->bsched = f->sched;
+      f->bshared = true;
+    } else if (st == GPTQ2D_OK) {
+      st = build_schedule(*f, gb, f->bsched);
+    }
   }
   if (st != GPTQ2D_OK) {
     free_all(f);

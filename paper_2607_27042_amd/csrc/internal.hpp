@@ -57,7 +57,9 @@ struct Factors {
   // first use) and the event that marks its end
   hipStream_t own = nullptr;
   hipEvent_t ev_own = nullptr;
-  Schedule sched;
+  Schedule sched;   // delivery plan of a round by itself
+  Schedule bsched;  // and in a batch (sched's device arrays where bshared)
+  bool bshared = false;
   // launch timing of the sweep's stage kernel (diagnostics): while enabled,
   // every stage launch records its start and end time stamps into a pair of
   // events; the pairs accumulate until they are read
@@ -145,7 +147,7 @@ void schedule_tasks(int MT, int NT, int g, std::vector<int4>& all, std::vector<i
 gptq2d_status pack_bins(int MT, int NT, int units, std::vector<int4>& all,
                         const std::vector<int>& offset, std::vector<int4>& bins,
                         std::vector<int>& bin_offset);
-gptq2d_status build_schedule(Factors& f, int g);
+gptq2d_status build_schedule(Factors& f, int g, Schedule& sched);
 void free_schedule(Schedule& s);
 // allow_timing = false: no stage-launch timing even if the handle asks for it
 // (timing creates HIP events on first use)

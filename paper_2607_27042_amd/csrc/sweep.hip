@@ -1224,7 +1224,7 @@ void free_schedule(Schedule& sc) {
   sc.d_base = nullptr;
 }
 
-gptq2d_status build_schedule(Factors& f, int g) {
+gptq2d_status build_schedule(Factors& f, int g, Schedule& sched) {
   std::vector<int4> all;
   std::vector<int> off;
   if (g < 1) g = 1;
@@ -1237,24 +1237,24 @@ gptq2d_status build_schedule(Factors& f, int g) {
   std::vector<int> boff;
   const gptq2d_status st = pack_bins(f.MT, f.NT, units, all, off, bins, boff);
   if (st != GPTQ2D_OK) return st;
-  free_schedule(f.sched);
+  free_schedule(sched);
   if (!all.empty()) {
-    hipError_t e = hipMalloc(&f.sched.d_tasks, all.size() * sizeof(int4));
+    hipError_t e = hipMalloc(&sched.d_tasks, all.size() * sizeof(int4));
     if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(f.sched.d_tasks, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice);
+    e = hipMemcpy(sched.d_tasks, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "schedule upload");
-    e = hipMalloc(&f.sched.d_bins, bins.size() * sizeof(int4));
+    e = hipMalloc(&sched.d_bins, bins.size() * sizeof(int4));
     if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(f.sched.d_bins, bins.data(), bins.size() * sizeof(int4), hipMemcpyHostToDevice);
+    e = hipMemcpy(sched.d_bins, bins.data(), bins.size() * sizeof(int4), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "schedule upload");
   }
   {
     const int S = f.MT + f.NT - 1;
     std::vector<int4> stab(S);
     for (int k = 0; k < S; ++k) stab[k] = int4{off[k], boff[k], boff[k + 1] - boff[k], 0};
-    hipError_t e = hipMalloc(&f.sched.d_stage, S * sizeof(int4));
+    hipError_t e = hipMalloc(&sched.d_stage, S * sizeof(int4));
     if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(f.sched.d_stage, stab.data(), S * sizeof(int4), hipMemcpyHostToDevice);
+    e = hipMemcpy(sched.d_stage, stab.data(), S * sizeof(int4), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "schedule upload");
     // the fixed stage arguments of the handle (batched rounding)
     StageArgs b{};
@@ -1268,19 +1268,19 @@ gptq2d_status build_schedule(Factors& f, int g) {
     b.U = f.U;
     b.dL = f.dL;
     b.dU = f.dU;
-    b.tasks = f.sched.d_tasks;
-    b.bins = f.sched.d_bins;
-    b.stab = f.sched.d_stage;
-    e = hipMalloc(&f.sched.d_base, sizeof(StageArgs));
+    b.tasks = sched.d_tasks;
+    b.bins = sched.d_bins;
+    b.stab = sched.d_stage;
+    e = hipMalloc(&sched.d_base, sizeof(StageArgs));
     if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(f.sched.d_base, &b, sizeof(StageArgs), hipMemcpyHostToDevice);
+    e = hipMemcpy(sched.d_base, &b, sizeof(StageArgs), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "schedule upload");
   }
-  f.sched.g = g;
-  f.sched.stages = f.MT + f.NT - 1;
-  f.sched.offset = off;
-  f.sched.bin_offset = boff;
-  f.sched.ntasks = all.size();
+  sched.g = g;
+  sched.stages = f.MT + f.NT - 1;
+  sched.offset = off;
+  sched.bin_offset = boff;
+  sched.ntasks = all.size();
   return GPTQ2D_OK;
 }
 
@@ -1327,11 +1327,12 @@ static StageArgs stage_args(const Factors& f, const void* X, int64_t ldx, int32_
   return a;
 }
 
-// work groups of stage k of a problem: the tile sweeps beside the delivery bins
+// work groups of stage k of a problem of a batch: the tile sweeps beside the
+// delivery bins
 static int stage_blocks(const Factors& f, int k) {
   int ilo, ihi;
   stage_rows(f.MT, f.NT, k, ilo, ihi);
-  return (ihi - ilo + 1) + (f.sched.bin_offset[k + 1] - f.sched.bin_offset[k]);
+  return (ihi - ilo + 1) + (f.bsched.bin_offset[k + 1] - f.bsched.bin_offset[k]);
 }
 
 template <typename T>
@@ -1406,7 +1407,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
     const Workspace ws = workspace_carve(*f[p], region);
     // X, Z, Y as the problem's sweep addresses them (mirrored in reverse order)
     const StageArgs a = stage_args<T>(*f[p], X[p], ldx[p], Z[p], ldz[p], Y ? Y[p] : nullptr, Y ? ldy[p] : 0, ws);
-    h[p] = BatchProb{(const StageArgs*)f[p]->sched.d_base, a.X, a.Z, a.Y, a.ldx, a.ldz, a.ldy, a.cstep, region};
+    h[p] = BatchProb{(const StageArgs*)f[p]->bsched.d_base, a.X, a.Z, a.Y, a.ldx, a.ldz, a.ldy, a.cstep, region};
     region += align256(workspace_bytes(*f[p]));
   }
   const gptq2d_status st = enqueue_upload(base, head.data(), head.size(), s);
@@ -1414,7 +1415,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
   for (int g0 = 0; g0 < count; g0 += BATCH_MAX) {
     const int cnt = std::min(BATCH_MAX, count - g0);
     int smax = 0;
-    for (int q = 0; q < cnt; ++q) smax = std::max(smax, f[g0 + q]->sched.stages);
+    for (int q = 0; q < cnt; ++q) smax = std::max(smax, f[g0 + q]->bsched.stages);
     BatchLaunch bl;
     bl.desc = desc + g0;
     bl.flags = flags;
@@ -1424,7 +1425,7 @@ static gptq2d_status round_batched_typed(int count, const Factors* const* f, con
       int tot = 0;
       for (int q = 0; q < cnt; ++q) {
         bl.off[q] = tot;
-        if (k < f[g0 + q]->sched.stages) tot += stage_blocks(*f[g0 + q], k);
+        if (k < f[g0 + q]->bsched.stages) tot += stage_blocks(*f[g0 + q], k);
       }
       bl.off[cnt] = tot;
       bl.stage = k;
