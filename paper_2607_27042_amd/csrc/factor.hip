@@ -58,7 +58,9 @@ struct FacProb {
   const FacStatic* base;
   const void* A;
   const void* B;
-  int64_t lda, ldb, rev;
+  int64_t lda2, ldb;  // lda2 = 2 lda + (rounding order reversed)
+  __host__ __device__ int64_t lda() const { return lda2 >> 1; }
+  __host__ __device__ int rev() const { return (int)(lda2 & 1); }
 };
 struct BatchCtx {
   const FacProb* tab;  // unused by single-problem launches
@@ -205,9 +207,9 @@ __global__ __launch_bounds__(NT) void k_gram(FacArgs f0, const T* A0, int64_t ld
   const FacArgs& f = BAT ? pb->base->f : f0;
   const T* A = BAT ? (const T*)pb->A : A0;
   const T* B = BAT ? (const T*)pb->B : B0;
-  const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
+  const int64_t lda = BAT ? pb->lda() : lda0, ldb = BAT ? pb->ldb : ldb0;
   const int bid = bat_block<BAT>(bc);
-  const int rev = BAT ? (int)pb->rev : f0.rev;
+  const int rev = BAT ? pb->rev() : f0.rev;
   const int t0 = (sides & 1) ? f.s[0].nb * (f.s[0].nb + 1) / 2 : 0;
   if (bid == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
   int bp, bq;
@@ -306,9 +308,9 @@ __global__ __launch_bounds__(NT) void k_gram32(FacArgs f0, const T* A0, int64_t 
   const FacArgs& f = BAT ? pb->base->f : f0;
   const T* A = BAT ? (const T*)pb->A : A0;
   const T* B = BAT ? (const T*)pb->B : B0;
-  const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
+  const int64_t lda = BAT ? pb->lda() : lda0, ldb = BAT ? pb->ldb : ldb0;
   const int bid = bat_block<BAT>(bc);
-  const int rev = BAT ? (int)pb->rev : f0.rev;
+  const int rev = BAT ? pb->rev() : f0.rev;
   const int n0 = f.s[0].dp / GT, t0 = (sides & 1) ? n0 * (n0 + 1) / 2 : 0;
   if (bid == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
   int bp, bq;
@@ -432,7 +434,7 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
   const FacArgs& f = BAT ? pb->base->f : f0;
   const T* A = BAT ? (const T*)pb->A : A0;
   const T* B = BAT ? (const T*)pb->B : B0;
-  const int64_t lda = BAT ? pb->lda : lda0, ldb = BAT ? pb->ldb : ldb0;
+  const int64_t lda = BAT ? pb->lda() : lda0, ldb = BAT ? pb->ldb : ldb0;
   const int n0 = (sides & 1) ? f.s[0].nb * f.s[0].nb : 0;
   int b = bat_block<BAT>(bc);
   if (b == 0 && threadIdx.x == 0) f.flags[0] = f.flags[1] = 0;
@@ -443,7 +445,7 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
   const int i0 = (b / nt) * TB, k0 = (b % nt) * TB;  // S rows i0.., columns k0..
   double* S = sd.li;
   const int t = threadIdx.x;
-  const int rev = BAT ? (int)pb->rev : f0.rev;
+  const int rev = BAT ? pb->rev() : f0.rev;
   bool nz = false;  // a nonzero entry in this thread's part of the block
   if (side == 0) {
     // A rows k0 + r, columns d-1-(i0+63) .. d-1-i0 (ascending; in reverse
@@ -960,7 +962,7 @@ struct DiagSmem {
 
 // The block in ds.Am (zero above the diagonal; ds.Wm zero) by one work group:
 // Cholesky factor in place, its inverse in ds.Wm.
-__device__ void diag_core(int* flags, DiagSmem& ds) {
+__device__ __forceinline__ void diag_core(int* flags, DiagSmem& ds) {
   constexpr int LD = DLD;
   double(*Am)[LD] = ds.Am;
   double(*Wm)[LD] = ds.Wm;
@@ -1028,7 +1030,7 @@ __device__ __forceinline__ void diag_store(const Side& sd, int kb, const DiagSme
 }
 
 // Diagonal block kb of one side by one work group.
-__device__ void diag_tile(const Side& sd, int kb, int* flags, DiagSmem& ds) {
+__device__ __forceinline__ void diag_tile(const Side& sd, int kb, int* flags, DiagSmem& ds) {
   const int t = threadIdx.x;
   double* blk = sd.gr + (int64_t)kb * TB * sd.dp + (int64_t)kb * TB;
   {
@@ -1065,7 +1067,7 @@ __global__ __launch_bounds__(NT) void k_one_block(FacArgs f0, const T* A0, int64
   const FacArgs& f = BAT ? pb->base->f : f0;
   const int side = bat_block<BAT>(bc), t = threadIdx.x;
   const Side sd = f.s[side];
-  const int rev = BAT ? (int)pb->rev : f0.rev, d = sd.d;
+  const int rev = BAT ? pb->rev() : f0.rev, d = sd.d;
   // an error word per side: the other side's work group may run at any time
   int* const flags = f.flags + side;
   if (t == 0) {
@@ -1076,7 +1078,7 @@ __global__ __launch_bounds__(NT) void k_one_block(FacArgs f0, const T* A0, int64
   acc.zero();
   double r[16];
   if (side == 0) {
-    gram_load<T, 0>(BAT ? (const T*)pb->A : A0, BAT ? pb->lda : lda0, d, 0, 0, r, rev);
+    gram_load<T, 0>(BAT ? (const T*)pb->A : A0, BAT ? pb->lda() : lda0, d, 0, 0, r, rev);
     put_ak(sm.st, r);
     put_b(sm.st, r);
   } else {
@@ -1559,8 +1561,9 @@ __global__ __launch_bounds__(NT) void k_finalize(FacArgs f0, BatchCtx bc) {
 }
 
 // Stream-ordered upload of up to PUT_WORDS 8-byte words that travel as
-// kernel arguments (no host buffer has to outlive the enqueueing call).
-constexpr int PUT_WORDS = 384;
+// kernel arguments (no host buffer has to outlive the enqueueing call); a
+// launch's arguments end at 4 KB, and each launch takes about 4.5 us.
+constexpr int PUT_WORDS = 504;
 struct PutArgs {
   uint64_t* dst;
   int n;
@@ -1918,7 +1921,7 @@ gptq2d_status launch_factor_batched(int count, Factors* const* fs, gptq2d_dtype 
   static_assert(sizeof(FacProb) % sizeof(uint64_t) == 0, "the table is uploaded in 8-byte words");
   std::vector<FacProb> h(count);
   for (int p = 0; p < count; ++p)
-    h[p] = FacProb{(const FacStatic*)fs[p]->d_fac, A[p], B[p], lda[p], ldb[p], fs[p]->rev};
+    h[p] = FacProb{(const FacStatic*)fs[p]->d_fac, A[p], B[p], 2 * lda[p] + (fs[p]->rev ? 1 : 0), ldb[p]};
   gptq2d_status st = enqueue_upload(table, h.data(), h.size() * sizeof(FacProb), s);
   if (st != GPTQ2D_OK) return st;
   return factor_impl(*fs[0], (const FacProb*)table, count, dt, nullptr, 0, nullptr, 0, s);

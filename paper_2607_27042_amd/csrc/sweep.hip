@@ -1166,18 +1166,21 @@ gptq2d_status pack_bins(int MT, int NTt, int units, std::vector<int4>& all,
     const double chunk = tiles == 4 ? kChunk4 : tiles == 2 ? kChunk2 : kChunk1;
     return ((x.x >> 1) & 1 ? kStartOw : kStartAdd) + chunk * (TB / KQ) * K;
   };
+  const int nb = std::max(1, units);
+  std::vector<std::vector<int>> member(nb);  // (kept between stages: no allocations in the loop)
+  std::vector<int> order;
+  std::vector<double> costs(all.size());
+  for (size_t i = 0; i < all.size(); ++i) costs[i] = cost(all[i]);
   for (int k = 0; k < S; ++k) {
     boff[k] = (int)bins.size();
     const int n = off[k + 1] - off[k];
     if (n == 0) continue;
     const int nsweep = std::min(k, MT - 1) - std::max(0, k - NTt + 1) + 1;
     const int nfree = std::max(0, units - nsweep);
-    const int nb = std::max(1, units);
-    std::vector<int> order(n);
+    order.resize(n);
     for (int i = 0; i < n; ++i) order[i] = off[k] + i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return cost(all[x]) > cost(all[y]); });
-    std::vector<std::vector<int>> member(nb);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return costs[x] > costs[y]; });
+    for (auto& m : member) m.clear();
     // least-loaded bin first (ties: lowest index)
     typedef std::pair<double, int> Load;
     std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
@@ -1186,7 +1189,7 @@ gptq2d_status pack_bins(int MT, int NTt, int units, std::vector<int4>& all,
       Load top = heap.top();
       heap.pop();
       member[top.second].push_back(i);
-      top.first += cost(all[i]);
+      top.first += costs[i];
       heap.push(top);
     }
     const int base = (int)out.size();
