@@ -1183,6 +1183,10 @@ struct UpdRange {
   int j0;  // S columns from j0 on (jb in [j0, k1))
   int dg;  // the diagonal block whose update completes here (qa), factored
            // by the same work group right after it; -1: none
+  int first;  // Q sums start from the old values instead of being subtracted from
+              // them: the same bits for every grouping of the panels, for sizes
+              // where one problem and a batch group them differently (elsewhere
+              // slower: 4096 4.30 against 4.28 ms, 8192 24.6 against 24.4)
 };
 
 __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, int& nq, int& ns) {
@@ -1193,17 +1197,17 @@ __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, in
 }
 
 // acc += sum over 64-deep blocks b of A_b op(B_b), A_b at pa + b*sa_, B_b at
-// pb + b*sb_; BT: B given transposed and the sum subtracted. Double-buffered
-// through LDS.
+// pb + b*sb_; BT: B given transposed; neg: the sum subtracted (BT only).
+// Double-buffered through LDS.
 template <int BT>
 __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_, const double* pb,
-                            int64_t ldb, int64_t sb_, int nb, Stage64* st) {
+                            int64_t ldb, int64_t sb_, int nb, Stage64* st, bool neg = false) {
   double ra[16], rb[16];
   load_blk(pa, lda, ra);
   load_blk(pb, ldb, rb);
   for (int b = 0; b < nb; ++b) {
     Stage64& s = st[b & 1];
-    if (BT) {
+    if (BT && neg) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) ra[i] = -ra[i];
     }
@@ -1252,12 +1256,20 @@ __global__ __launch_bounds__(NT) void k_update(FacArgs f0, UpdRange r, BatchCtx 
     }
     const int bi = bj + b;
     double* out = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)bj * TB;
-    // the sum starts from the old value, here and in the far update: its terms
-    // come in the order of the panels however they are grouped into launches,
-    // so one problem and a batch get the same bits by different routes
-    acc_add_from(acc, out, sd.dp);
-    gemm_blocks<1>(acc, sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)r.k0 * TB, sd.dp, TB,
-                   sd.gr + (int64_t)bj * TB * sd.dp + (int64_t)r.k0 * TB, sd.dp, TB, k1 - r.k0, st);
+    const double* pa = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)r.k0 * TB;
+    const double* pb = sd.gr + (int64_t)bj * TB * sd.dp + (int64_t)r.k0 * TB;
+    if (r.first) {
+      // (as the far update does: the terms come in the order of the panels)
+      acc_add_from(acc, out, sd.dp);
+      gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st, true);
+    } else {
+      Acc old;
+      old.zero();
+      acc_add_from(old, out, sd.dp);
+      gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc.t[i] = old.t[i] - acc.t[i];
+    }
     if (bi == r.dg && bj == r.dg) {
       // no other work group of this launch reads this block (their operands
       // are columns before k1 <= dg): it goes to its factorisation in LDS
@@ -1581,7 +1593,7 @@ __global__ void k_put(PutArgs p) {
 //   8192 (groups of eight): 24143 / 25398 / -
 // Right-looking, each update on the chain is one product deep instead of up to
 // four; from some size on its extra tiles take the device from the far updates.
-// A batch fills the device and stays left-looking: fewer passes over memory.
+// A batch of up to 24 block columns stays left-looking: fewer passes over memory.
 constexpr int kRightLooking = 64;
 constexpr int kOneGroup = 24;
 
@@ -1782,6 +1794,9 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
                            (const double*)A, lda, (const double*)B, ldb, slow, bc);
     });
   }
+  const bool right = nbmax <= kRightLooking && (!tab || nbmax > kOneGroup);
+  const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
+  const int first = nbmax <= kOneGroup;
   auto update = [&](const UpdRange& r, hipStream_t st) {
     go(h_upd_count(nb0, r) + h_upd_count(nb1, r), st, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t q) {
       constexpr bool BT = decltype(bat)::value;
@@ -1817,7 +1832,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_update128<BT>), g, dim3(UT), 0, st, a, g0, g1, ga, gb, nfar, bc);
       });
     }
-    update(UpdRange{ga, ga, ga, gb, g0, g1, g0, -1}, st0);
+    update(UpdRange{ga, ga, ga, gb, g0, g1, g0, -1, first}, st0);
   };
   // Groups of GROUP panels (an even count: the far part works on pairs of
   // block columns). Inside a group, before each panel, its column of Q and
@@ -1830,8 +1845,6 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   // the next group's near update writes those columns and waits for that
   // part only, not for the rest behind it. Eight panels per group from 96
   // block columns on (measured faster at 8192), four below (at 4096).
-  const bool right = !tab && nbmax <= kRightLooking;
-  const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
   hipError_t he = hipSuccess;
   bool far_pending = false, far1_pending = false;
   for (int g0 = 0; g0 < nbmax; g0 += GROUP) {
@@ -1857,8 +1870,8 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       // right-looking: every later column of the group receives the panel just
       // finished, one product deep
       if (kb + 1 < g1) {
-        if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1}, s);
-        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1}, s);
+        if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1, first}, s);
+        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1, first}, s);
       }
     }
     if (far1_pending) {
@@ -1871,7 +1884,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     // the next group's columns (the near update, on this stream: they are
     // needed first; 64 x 64 tiles, the first diagonal block factored by the
     // work group that completes it)
-    update(UpdRange{g1, g2, g1, g2, g0, g1, 0, g1}, s);
+    update(UpdRange{g1, g2, g1, g2, g0, g1, 0, g1, first}, s);
     if (g2 < nbmax) {
       he = hipEventRecord(f.ev_near, s);
       if (he == hipSuccess) he = hipStreamWaitEvent(f.aux, f.ev_near, 0);
