@@ -452,6 +452,15 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
     // order i0 .. i0+63), coalesced
     // (c0 < 0 or past the end: the padding, zeros)
     const int c0 = rev ? i0 : d - i0 - TB;
+    if (d == dp) {  // no padding, no checks (4096: 57 against 117 us)
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int e = t + NT * u, r = e >> 6, c = e & 63;
+        const double x = (double)A[(int64_t)(k0 + r) * lda + c0 + c];
+        tile[r][c] = x;
+        nz |= x != 0.0;
+      }
+    } else
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int e = t + NT * u, r = e >> 6, c = e & 63;  // c: column offset in A
@@ -467,6 +476,15 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
     for (int u = 0; u < 16; ++u) {
       const int e = t + NT * u, i = e >> 6, k = e & 63;
       S[(int64_t)(i0 + i) * dp + k0 + k] = tile[k][rev ? i : TB - 1 - i];
+    }
+  } else if (d == dp) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = t + NT * u, i = e >> 6, k = e & 63;
+      const int row = rev ? i0 + i : d - 1 - (i0 + i);
+      const double x = (double)B[(int64_t)row * ldb + k0 + k];
+      S[(int64_t)(i0 + i) * dp + k0 + k] = x;
+      nz |= x != 0.0;
     }
   } else {
 #pragma unroll
