@@ -1201,10 +1201,7 @@ struct UpdRange {
   int j0;  // S columns from j0 on (jb in [j0, k1))
   int dg;  // the diagonal block whose update completes here (qa), factored
            // by the same work group right after it; -1: none
-  int first;  // Q sums start from the old values instead of being subtracted from
-              // them: the same bits for every grouping of the panels, for sizes
-              // where one problem and a batch group them differently (elsewhere
-              // slower: 4096 4.30 against 4.28 ms, 8192 24.6 against 24.4)
+  int each;  // Q: every panel's sum is subtracted by itself (0: their total)
 };
 
 __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, int& nq, int& ns) {
@@ -1215,20 +1212,17 @@ __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, in
 }
 
 // acc += sum over 64-deep blocks b of A_b op(B_b), A_b at pa + b*sa_, B_b at
-// pb + b*sb_; BT: B given transposed; neg: the sum subtracted (BT only).
-// Double-buffered through LDS.
+// pb + b*sb_; BT: B given transposed. Double-buffered through LDS.
+// each: old -= the sum so far after every block but the last, the sum starts again.
 template <int BT>
 __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_, const double* pb,
-                            int64_t ldb, int64_t sb_, int nb, Stage64* st, bool neg = false) {
+                            int64_t ldb, int64_t sb_, int nb, Stage64* st, Acc* old = nullptr,
+                            bool each = false) {
   double ra[16], rb[16];
   load_blk(pa, lda, ra);
   load_blk(pb, ldb, rb);
   for (int b = 0; b < nb; ++b) {
     Stage64& s = st[b & 1];
-    if (BT && neg) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) ra[i] = -ra[i];
-    }
     put_a(s, ra);
     if (BT) put_bt(s, rb);
     else put_b(s, rb);
@@ -1238,6 +1232,11 @@ __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_
       load_blk(pb + (b + 1) * sb_, ldb, rb);
     }
     mma_blk(acc, s);
+    if (each && b + 1 < nb) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) old->t[i] -= acc.t[i];
+      acc.zero();
+    }
   }
 }
 
@@ -1276,18 +1275,12 @@ __global__ __launch_bounds__(NT) void k_update(FacArgs f0, UpdRange r, BatchCtx 
     double* out = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)bj * TB;
     const double* pa = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)r.k0 * TB;
     const double* pb = sd.gr + (int64_t)bj * TB * sd.dp + (int64_t)r.k0 * TB;
-    if (r.first) {
-      // (as the far update does: the terms come in the order of the panels)
-      acc_add_from(acc, out, sd.dp);
-      gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st, true);
-    } else {
-      Acc old;
-      old.zero();
-      acc_add_from(old, out, sd.dp);
-      gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st);
+    Acc old;
+    old.zero();
+    acc_add_from(old, out, sd.dp);
+    gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st, &old, r.each);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc.t[i] = old.t[i] - acc.t[i];
-    }
+    for (int i = 0; i < 4; ++i) acc.t[i] = old.t[i] - acc.t[i];
     if (bi == r.dg && bj == r.dg) {
       // no other work group of this launch reads this block (their operands
       // are columns before k1 <= dg): it goes to its factorisation in LDS
@@ -1328,9 +1321,10 @@ __global__ __launch_bounds__(NT) void k_update(FacArgs f0, UpdRange r, BatchCtx 
 //   Q tiles (BI >= BJ, g2/2 <= BJ < g3/2):  Q -= Lc[BI][g0:g1] Lc[BJ][g0:g1]^T
 //   S tiles (g2/2 <= BI < g3/2, BJ < g0/2): S += Lc[BI][g0:g1] Li[g0:g1][BJ]
 // with the same meaning as in k_update (the group's own S columns stay
-// there). Four waves, each a 64 x 64 quadrant as 4 x 4 MFMA blocks; the
+// there). Eight waves, each a 64 x 32 part as 4 x 2 MFMA blocks; the
 // accumulators start from the old values (the left operand enters negated
-// for Q); 32-deep chunks of both operands by direct global -> LDS loads,
+// for Q) or, where k_update subtracts panel by panel, from zero for each panel;
+// 32-deep chunks of both operands by direct global -> LDS loads,
 // double-buffered, in the layouts of the Gram tiles (rows with a contiguous
 // contraction index) and, for the right operand of S, rows of Li (b[k][j]).
 // A tile past the last block row / column (odd block count) is loaded from
@@ -1375,16 +1369,18 @@ __device__ __forceinline__ void upd_issue(const double* Ap, int64_t lda, const d
 
 // One 128 x 128 tile: wave w computes rows 64 qr .., columns 64 qc + 32 h ..
 // (qr = (w >> 1) & 1, qc = w & 1, h = w >> 2) as 4 x 2 MFMA blocks.
-template <int BT>
-__device__ void upd_tile(double* out, int64_t ldo, const double* Ap, int64_t lda, const double* Bp,
-                         int64_t ldb, int K, int nr, int nc, bool diag, UpdChunk* buf) {
+// EACH (Q): every 64-deep panel's sum is formed from zero and then added.
+template <int BT, bool EACH>
+__device__ __forceinline__ void upd_tile(double* out, int64_t ldo, const double* Ap, int64_t lda,
+                                         const double* Bp, int64_t ldb, int K, int nr, int nc, bool diag,
+                                         UpdChunk* buf) {
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
   const int qr = (w >> 1) & 1, qc = w & 1, h = w >> 2, r0 = l & 15, rr = r0 & 3;
   const bool mine = qr < nr && qc < nc && !(diag && qr < qc);
   const double sgn = BT ? -1.0 : 1.0;
   const int cb = 64 * qc + 32 * h;
   double* o = out + (int64_t)(64 * qr + (l >> 4)) * ldo + cb + (l & 15);
-  d4 acc[4][2];
+  d4 acc[4][2], old[EACH ? 4 : 1][2];
   upd_issue<BT>(Ap, lda, Bp, ldb, 0, nr, nc, buf[0], w, l);
   if (mine) {
 #pragma unroll
@@ -1394,11 +1390,20 @@ __device__ void upd_tile(double* out, int64_t ldo, const double* Ap, int64_t lda
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][j][r] = o[(int64_t)(16 * i + 4 * r) * ldo + 16 * j];
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): no wait for them inside the loop
+    if (EACH) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          old[EACH ? i : 0][j] = acc[i][j];
+          acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+      for (int j = 0; j < 2; ++j) acc[i][j] = old[EACH ? i : 0][j] = d4{0.0, 0.0, 0.0, 0.0};
   }
   const int nch = K / GQ;
   for (int c = 0; c < nch; ++c) {
@@ -1449,6 +1454,15 @@ __device__ void upd_tile(double* out, int64_t ldo, const double* Ap, int64_t lda
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // buffer refilled next
+    if (EACH && (c + 1) % (TB / GQ) == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          old[EACH ? i : 0][j] += acc[i][j];
+          acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+    }
   }
   if (mine) {
 #pragma unroll
@@ -1456,7 +1470,8 @@ __device__ void upd_tile(double* out, int64_t ldo, const double* Ap, int64_t lda
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[(int64_t)(16 * i + 4 * r) * ldo + 16 * j] = acc[i][j][r];
+        for (int r = 0; r < 4; ++r)
+          o[(int64_t)(16 * i + 4 * r) * ldo + 16 * j] = (EACH ? old[EACH ? i : 0][j] : acc[i][j])[r];
   }
 }
 
@@ -1467,7 +1482,9 @@ __host__ __device__ __forceinline__ int far_q_count(int nb2, int t0, int t1) {
   return t1 >= nb2 ? (nb2 - t0) * (nb2 - t0 + 1) / 2 : (t1 - t0) * (2 * nb2 - t0 - t1 + 1) / 2;
 }
 
-__device__ void update128_tile(const FacArgs& f, int g0, int g1, int g2, int g3, int b, UpdChunk* buf) {
+template <bool EACH>
+__device__ __forceinline__ void update128_tile(const FacArgs& f, int g0, int g1, int g2, int g3, int b,
+                                               UpdChunk* buf) {
   for (int s = 0; s < 2; ++s) {
     const Side& sd = f.s[s];
     const int nb = sd.nb;
@@ -1492,19 +1509,19 @@ __device__ void update128_tile(const FacArgs& f, int g0, int g1, int g2, int g3,
         }
         BI = BJ + b;
       }
-      upd_tile<1>(sd.gr + (int64_t)128 * BI * dp + 128 * BJ, dp,
-                  sd.gr + (int64_t)128 * BI * dp + TB * g0, dp,
-                  sd.gr + (int64_t)128 * BJ * dp + TB * g0, dp, K,
-                  min(2, nb - 2 * BI), min(2, nb - 2 * BJ), BI == BJ, buf);
+      upd_tile<1, EACH>(sd.gr + (int64_t)128 * BI * dp + 128 * BJ, dp,
+                        sd.gr + (int64_t)128 * BI * dp + TB * g0, dp,
+                        sd.gr + (int64_t)128 * BJ * dp + TB * g0, dp, K,
+                        min(2, nb - 2 * BI), min(2, nb - 2 * BJ), BI == BJ, buf);
       return;
     }
     b -= nq;
     if (b < ns) {
       const int BI = t0 + b / (g0 / 2), BJ = b % (g0 / 2);
-      upd_tile<0>(sd.li + (int64_t)128 * BI * dp + 128 * BJ, dp,
-                  sd.gr + (int64_t)128 * BI * dp + TB * g0, dp,
-                  sd.li + (int64_t)TB * g0 * dp + 128 * BJ, dp, K,
-                  min(2, nb - 2 * BI), 2, false, buf);
+      upd_tile<0, false>(sd.li + (int64_t)128 * BI * dp + 128 * BJ, dp,
+                         sd.gr + (int64_t)128 * BI * dp + TB * g0, dp,
+                         sd.li + (int64_t)TB * g0 * dp + 128 * BJ, dp, K,
+                         min(2, nb - 2 * BI), 2, false, buf);
       return;
     }
     b -= ns;
@@ -1514,7 +1531,7 @@ __device__ void update128_tile(const FacArgs& f, int g0, int g1, int g2, int g3,
 // ntile tiles over the grid, tile b by work group b mod gridDim.x: a grid
 // smaller than the device leaves compute units to the diagonal blocks and
 // panels that run beside it on the other stream
-template <bool BAT>
+template <bool BAT, bool EACH>
 __global__ __launch_bounds__(UT) void k_update128(FacArgs f0, int g0, int g1, int g2, int g3, int ntile,
                                                   BatchCtx bc) {
   __shared__ UpdChunk buf[2];
@@ -1527,7 +1544,7 @@ __global__ __launch_bounds__(UT) void k_update128(FacArgs f0, int g0, int g1, in
   const int pos = x * q8 + min(x, r8) + bid / 8;
   for (int b = pos; b < ntile; b += grid) {
     if (b != pos) __syncthreads();  // the staging buffers are reused
-    update128_tile(f, g0, g1, g2, g3, b, buf);
+    update128_tile<EACH>(f, g0, g1, g2, g3, b, buf);
   }
 }
 
@@ -1814,7 +1831,12 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   }
   const bool right = nbmax <= kRightLooking && (!tab || nbmax > kOneGroup);
   const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
-  const int first = nbmax <= kOneGroup;
+  // A single problem of one group subtracts one panel's product after another from
+  // Q; a batch, which takes more of them per pass, then subtracts each by itself,
+  // too: the same bits. (Started from the old values instead, every term would
+  // round at Q's magnitude: factors of a triangular 512 basis 5.1e-15 from long
+  // double, now 3.2e-15, the times level.)
+  const int each = nbmax <= kOneGroup;
   auto update = [&](const UpdRange& r, hipStream_t st) {
     go(h_upd_count(nb0, r) + h_upd_count(nb1, r), st, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t q) {
       constexpr bool BT = decltype(bat)::value;
@@ -1847,10 +1869,14 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       }
       go(grid, st0, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
         constexpr bool BT = decltype(bat)::value;
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_update128<BT>), g, dim3(UT), 0, st, a, g0, g1, ga, gb, nfar, bc);
+        if (BT && each)
+          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_update128<BT, BT>), g, dim3(UT), 0, st, a, g0, g1, ga, gb, nfar, bc);
+        else
+          hipLaunchKernelGGL(HIP_KERNEL_NAME(k_update128<BT, false>), g, dim3(UT), 0, st, a, g0, g1, ga, gb, nfar,
+                             bc);
       });
     }
-    update(UpdRange{ga, ga, ga, gb, g0, g1, g0, -1, first}, st0);
+    update(UpdRange{ga, ga, ga, gb, g0, g1, g0, -1, each}, st0);
   };
   // Groups of GROUP panels (an even count: the far part works on pairs of
   // block columns). Inside a group, before each panel, its column of Q and
@@ -1888,8 +1914,8 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       // right-looking: every later column of the group receives the panel just
       // finished, one product deep
       if (kb + 1 < g1) {
-        if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1, first}, s);
-        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1, first}, s);
+        if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1, 0}, s);
+        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1, each}, s);
       }
     }
     if (far1_pending) {
@@ -1902,7 +1928,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     // the next group's columns (the near update, on this stream: they are
     // needed first; 64 x 64 tiles, the first diagonal block factored by the
     // work group that completes it)
-    update(UpdRange{g1, g2, g1, g2, g0, g1, 0, g1, first}, s);
+    update(UpdRange{g1, g2, g1, g2, g0, g1, 0, g1, each}, s);
     if (g2 < nbmax) {
       he = hipEventRecord(f.ev_near, s);
       if (he == hipSuccess) he = hipStreamWaitEvent(f.aux, f.ev_near, 0);
