@@ -1628,9 +1628,14 @@ __global__ void k_put(PutArgs p) {
 //   8192 (groups of eight): 24143 / 25398 / -
 // Right-looking, each update on the chain is one product deep instead of up to
 // four; from some size on its extra tiles take the device from the far updates.
-// A batch of up to 24 block columns stays left-looking: fewer passes over memory.
+// A batch stays left-looking, for the fewer passes over memory: always up to 24
+// block columns, above them from four problems on (right-looking / left-looking
+// groups of four: 2 of 1700 x 1700 1318 / 1362, 2 of 768 x 3000 2497 / 2539, 3 of
+// 2048 x 2048 2923 / 2941, 4 2756 / 2658, 4 of 1024 x 4096 7847 / 7675, 6 of 1700 x
+// 1700 2768 / 2660).
 constexpr int kRightLooking = 64;
 constexpr int kOneGroup = 24;
+constexpr int kLeftBatch = 4;
 
 static gptq2d_status check_launch(const char* what);
 
@@ -1829,14 +1834,14 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
                            (const double*)A, lda, (const double*)B, ldb, slow, bc);
     });
   }
-  const bool right = nbmax <= kRightLooking && (!tab || nbmax > kOneGroup);
+  const bool right = nbmax <= kRightLooking && (!tab || (nbmax > kOneGroup && count < kLeftBatch));
   const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
-  // A single problem of one group subtracts one panel's product after another from
-  // Q; a batch, which takes more of them per pass, then subtracts each by itself,
-  // too: the same bits. (Started from the old values instead, every term would
+  // A right-looking problem subtracts one panel's product after another from Q (with
+  // one group all of them); a batch, which takes more of them per pass, then
+  // subtracts each by itself, too: the same bits. (Started from the old values instead, every term would
   // round at Q's magnitude: factors of a triangular 512 basis 5.1e-15 from long
   // double, now 3.2e-15, the times level.)
-  const int each = nbmax <= kOneGroup;
+  const int each = nbmax <= kOneGroup, each_in = nbmax <= kRightLooking;
   auto update = [&](const UpdRange& r, hipStream_t st) {
     go(h_upd_count(nb0, r) + h_upd_count(nb1, r), st, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t q) {
       constexpr bool BT = decltype(bat)::value;
@@ -1915,7 +1920,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       // finished, one product deep
       if (kb + 1 < g1) {
         if (right) update(UpdRange{kb + 1, g1, kb + 1, g1, kb, kb + 1, 0, kb + 1, 0}, s);
-        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1, each}, s);
+        else update(UpdRange{kb + 1, kb + 2, kb + 1, kb + 2, g0, kb + 1, 0, kb + 1, each_in}, s);
       }
     }
     if (far1_pending) {

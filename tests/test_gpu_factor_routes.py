@@ -32,7 +32,8 @@ def test_routes_match_oracle(m, n, reverse):
     np.testing.assert_allclose(lamU, lamUo, rtol=1e-10)
 
 
-@pytest.mark.parametrize("m,n,count", [(512, 384, 18), (130, 70, 160), (64, 40, 300), (1152, 64, 2)])
+@pytest.mark.parametrize("m,n,count", [(512, 384, 18), (130, 70, 160), (64, 40, 300), (1152, 64, 2), (1650, 300, 3),
+                                       (1650, 300, 4), (200, 2112, 5)])
 def test_batch_routes_same_bits(m, n, count):
     g = torch.Generator(device="cuda").manual_seed(7)
 
