@@ -1766,14 +1766,20 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     });
     return check_launch("factorisation launch");
   }
-  // Gram: small sides on 32 x 32 tiles (in a batch that fills the device, on
-  // 64 x 64 tiles) straight from the input, larger ones through the prepared
-  // panel and 128 x 128 tiles
+  // Gram: small sides on 32 x 32 or 64 x 64 tiles straight from the input, larger
+  // ones through the prepared panel and 128 x 128 tiles
   const int fast = fast_sides(f.m, f.n);
-  // a batch whose 64 x 64 tiles fill the device by themselves takes those: half
-  // the loads per product, and the same sums in the same order (64 problems of
-  // 512 x 384: the call 2.05 instead of 2.14 ms)
-  const bool many = (int64_t)tri * (tab ? count : 1) >= 4 * (int64_t)f.cus;
+  // A batch whose 64 x 64 tiles fill the device takes those: half the loads per
+  // product, zero blocks skipped, the same sums in the same order. Factorisations in
+  // us on 32 x 32 / 64 x 64 tiles, triangular bases, by tiles of 64 x 64 per compute
+  // unit: 512, 2 problems (0.6) 305 / 308, 384, 4 (0.7) 238 / 238, 448, 8 (1.8)
+  // 312 / 287, 640, 4 (1.7) 444 / 414, 448, 16 (3.5) 415 / 371, 960, 4 (3.8)
+  // 843 / 732. (The sides of one problem have 1.1 per unit at most; those of more
+  // than kSmallGram columns have tiles of their own and do not count.)
+  int64_t tiles = 0;
+  for (int sd = 0; sd < 2; ++sd)
+    if (a.s[sd].d <= kSmallGram) tiles += (int64_t)(tab ? count : 1) * (a.s[sd].nb * (a.s[sd].nb + 1) / 2);
+  const bool many = 4 * tiles >= 5 * (int64_t)f.cus;
   int small = 0, slow = 0, nprep = 0, nslow = 0, nsmall = 0;
   for (int sd = 0; sd < 2; ++sd) {
     const int d = a.s[sd].d, nb = a.s[sd].nb;

@@ -51,6 +51,18 @@ def test_batch_routes_same_bits(m, n, count):
             assert torch.equal(x, y), f"problem {p}"
 
 
+def test_small_side_beside_a_large_one():
+    """Each side's Gram takes the route of its own size: the factors of a 200 side
+    do not depend on the other side, but for the order of the panels' sums."""
+    m, n = 200, 2944
+    p, q = wl.random_problem(m, 64, 43, "f32", "general"), wl.random_problem(64, n, 44, "f32", "general")
+    both = binding.Factors.from_bases(pr.to_dev(p.A), pr.to_dev(q.B)).export()
+    left = binding.Factors.from_bases(pr.to_dev(p.A), pr.to_dev(p.B)).export()
+    right = binding.Factors.from_bases(pr.to_dev(q.A), pr.to_dev(q.B)).export()
+    for got, ref in ((both[0], left[0]), (both[1], right[1]), (both[2], left[2]), (both[3], right[3])):
+        assert (got - ref).abs().max() <= 1e-12 * ref.abs().max()
+
+
 @pytest.mark.parametrize("side", ["A", "B"])
 @pytest.mark.parametrize("m,n", [(20, 64), (64, 96)])
 def test_singular_side_is_reported(side, m, n):
