@@ -371,6 +371,7 @@ struct GramPlan {
   int nch0, nch1;      // dense chunks per tile on each side
   int64_t units;       // dense units: t0 nch0 + t1 nch1
   int G;               // launch grid (work groups, an upper bound for the ranges)
+  int whole;           // a work group per tile: no ranges, nothing split
 };
 
 // The envelope and plan buffer of a handle (ints): the total of units (an
@@ -694,29 +695,54 @@ __device__ __forceinline__ double* gram_slot(double* part, int slot, int h) {
   return part + ((int64_t)(2 * slot + h) << 14) + threadIdx.x;
 }
 
+// The b-th tile of a problem on whole tiles: the sides in turn, each from its
+// longer end (a triangular basis has its longest tiles at one of them).
+__device__ __forceinline__ int gram_whole_tile(const GramView& v, const GramPlan& pl, int b) {
+  const int both = 2 * min(pl.t0, pl.t1);
+  const int side = b < both ? b & 1 : pl.t1 > pl.t0;
+  const int first = side ? pl.t0 : 0, n = side ? pl.t1 : pl.t0, i = b < both ? b >> 1 : b - both / 2;
+  const long long head = v.pre[first + 1] - v.pre[first], tail = v.pre[first + n] - v.pre[first + n - 1];
+  return first + (head < tail ? n - 1 - i : i);
+}
+
+// On whole tiles (batches only) the launch starts with every problem's longest tile:
+// 16 triangular problems of 1024 x 1024 1830 us with that order, 2062 with a
+// problem's tiles one after another, where an XCD gets the same ones of all.
 template <bool BAT>
 __global__ __launch_bounds__(NT) void k_gram128(FacArgs f0, GramPlan pl, double* part0, BatchCtx bc) {
   __shared__ GramChunk buf[2];
-  const FacProb* pb = bat_prob<BAT>(bc);
+  const bool whole = BAT && pl.whole;
+  const int probs = whole ? (int)gridDim.x / bc.per : 1;
+  const FacProb* pb = whole ? bc.tab + blockIdx.x % probs : bat_prob<BAT>(bc);
   const FacArgs& f = BAT ? pb->base->f : f0;
   double* part = BAT ? pb->base->gpart : part0;
   const GramView v = gram_view(f.genv, pl);
-  const int bid = bat_block<BAT>(bc);
-  const int G = *v.Geff, T = pl.t0 + pl.t1;
-  const long long U = *v.U;
-  // work groups are dealt round-robin to the eight L2 domains (XCDs): give
-  // each domain a contiguous run of ranges, so that the tiles it runs at the
-  // same time share their row panel (tri_index enumerates row by row)
-  // (domain x holds the work groups i = x mod 8 and gets q ranges, plus one
-  // when x < r, from x q + min(x, r) on, with q, r the quotient and remainder
-  // of G by 8; the launch's further work groups have none)
-  const int q8 = G / 8, r8 = G % 8;
-  const int x = bid % 8, y = bid / 8;
-  if (y >= q8 + (x < r8 ? 1 : 0)) return;
-  const int jr = x * q8 + min(x, r8) + y;
-  const long long lo = U * jr / G, hi = U * (jr + 1) / G;
+  const int T = pl.t0 + pl.t1;
+  int jr, tile;  // range, its first tile
+  long long lo, hi;
+  if (whole) {
+    jr = tile = gram_whole_tile(v, pl, (int)blockIdx.x / probs);
+    lo = v.pre[tile];
+    hi = v.pre[tile + 1];
+  } else {
+    const int bid = bat_block<BAT>(bc);
+    const int G = *v.Geff;
+    const long long U = *v.U;
+    // work groups are dealt round-robin to the eight L2 domains (XCDs): give
+    // each domain a contiguous run of ranges, so that the tiles it runs at the
+    // same time share their row panel (tri_index enumerates row by row)
+    // (domain x holds the work groups i = x mod 8 and gets q ranges, plus one
+    // when x < r, from x q + min(x, r) on, with q, r the quotient and remainder
+    // of G by 8; the launch's further work groups have none)
+    const int q8 = G / 8, r8 = G % 8;
+    const int x = bid % 8, y = bid / 8;
+    if (y >= q8 + (x < r8 ? 1 : 0)) return;
+    jr = x * q8 + min(x, r8) + y;
+    lo = U * jr / G;
+    hi = U * (jr + 1) / G;
+    tile = lo < hi ? gram_tile_of(v.pre, T, lo) : 0;
+  }
   d4 acc[4][4];
-  int tile = lo < hi ? gram_tile_of(v.pre, T, lo) : 0;
   for (long long u = lo; u < hi; ++tile) {
     const int side = tile < pl.t0 ? 0 : 1;
     const Side& sd = f.s[side];
@@ -775,8 +801,9 @@ __global__ __launch_bounds__(NT) void k_gram_fix(FacArgs f0, GramPlan pl, const 
   gram_store(f.s[side], bp, bq, acc);
 }
 
-static GramPlan gram_plan(int m, int n, int fast, int cus) {
+static GramPlan gram_plan(int m, int n, int fast, int whole, int cus) {
   GramPlan pl;
+  pl.whole = whole;
   pl.b0 = (fast & 1) ? (m + TB - 1) / TB : 0;
   pl.b1 = (fast & 2) ? (n + TB - 1) / TB : 0;
   pl.n0 = (pl.b0 + 1) / 2;
@@ -788,30 +815,37 @@ static GramPlan gram_plan(int m, int n, int fast, int cus) {
   pl.units = (int64_t)pl.t0 * pl.nch0 + (int64_t)pl.t1 * pl.nch1;
   const int64_t nmax = std::max(pl.t0 ? pl.nch0 : 1, pl.t1 ? pl.nch1 : 1);
   // every range at least one dense tile long: a tile meets at most one boundary
-  pl.G = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(cus, 1), pl.units / nmax));
+  pl.G = whole ? pl.t0 + pl.t1
+               : (int)std::max<int64_t>(1, std::min<int64_t>(std::max(cus, 1), pl.units / nmax));
   return pl;
 }
 
-// Up to this dimension a side's Gram runs on 32 x 32 tiles (512 x 384: the Gram's
-// launches 102 -> 14 us; the 136 tiles of a 1024 side still leave the 128 x 128
-// route with fewer work groups than compute units).
+// Up to this dimension a problem's Gram runs on 32 x 32 tiles (512 x 384: the Gram's
+// launches 102 -> 14 us; a 1024 side has 36 tiles of 128 x 128, which leave most
+// compute units idle, and 528 of 32 x 32: both sides of 1024 x 1024 480 against
+// 670 us for the whole factorisation).
 constexpr int kSmallGram = 1024;
+// In a batch, sides of whole 128 x 128 tiles over 448 take them where they fill the
+// device (factor_impl has the measurements).
+constexpr int kWholeGram = 448;
 
-static int fast_sides(int m, int n) {
-  return (m > kSmallGram ? 1 : 0) | (n > kSmallGram ? 2 : 0);
+static int sides_over(int d, int m, int n) { return (m > d ? 1 : 0) | (n > d ? 2 : 0); }
+static int fast_sides(int m, int n) { return sides_over(kSmallGram, m, n); }
+static int whole_sides(int m, int n) {
+  return fast_sides(m, n) ? 0 : sides_over(kWholeGram, m % 128 ? 0 : m, n % 128 ? 0 : n);
 }
 
 size_t gram_part_doubles(int m, int n, int cus) {
   const int fast = fast_sides(m, n);
   if (!fast) return 0;
-  const GramPlan pl = gram_plan(m, n, fast, cus);
+  const GramPlan pl = gram_plan(m, n, fast, 0, cus);
   return pl.G > 1 ? (size_t)2 * pl.G * 16384 : 0;
 }
 
 size_t gram_env_ints(int m, int n) {
-  const int fast = fast_sides(m, n);
+  const int fast = fast_sides(m, n) | whole_sides(m, n);
   if (!fast) return 0;
-  const GramPlan pl = gram_plan(m, n, fast, 1);
+  const GramPlan pl = gram_plan(m, n, fast, 0, 1);
   return gram_view_ints(pl.n0, pl.n1, pl.t0 + pl.t1);
 }
 
@@ -1768,26 +1802,43 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   }
   // Gram: small sides on 32 x 32 or 64 x 64 tiles straight from the input, larger
   // ones through the prepared panel and 128 x 128 tiles
-  const int fast = fast_sides(f.m, f.n);
-  // A batch whose 64 x 64 tiles fill the device takes those: half the loads per
-  // product, zero blocks skipped, the same sums in the same order. Factorisations in
-  // us on 32 x 32 / 64 x 64 tiles, triangular bases, by tiles of 64 x 64 per compute
-  // unit: 512, 2 problems (0.6) 305 / 308, 384, 4 (0.7) 238 / 238, 448, 8 (1.8)
-  // 312 / 287, 640, 4 (1.7) 444 / 414, 448, 16 (3.5) 415 / 371, 960, 4 (3.8)
-  // 843 / 732. (The sides of one problem have 1.1 per unit at most; those of more
-  // than kSmallGram columns have tiles of their own and do not count.)
-  int64_t tiles = 0;
+  int fast = fast_sides(f.m, f.n);
+  const int64_t problems = tab ? count : 1;
+  // A batch that fills the device takes larger tiles: fewer loads per product, zero
+  // blocks skipped, the same sums in the same order. Factorisations in us on 32 x 32 /
+  // 64 x 64 / whole 128 x 128 tiles, by tiles of 64 and of 128 per compute unit,
+  // dense bases (triangular ones):
+  //   512, 2 problems (0.6, 0.2) 305 / 311 / 354 (305 / 308 / 352)
+  //   640, 4 (1.7, 0.5) 445 / 427 / 458 (444 / 414 / 456)
+  //   896, 4 (3.3, 0.9) 751 / 720 / 675 (749 / 670 / 670)
+  //   768, 8 (4.9, 1.3) 794 / 733 / 754 (792 / 681 / 671)
+  //   640, 16 (6.9, 1.9) 897 / 815 / 786 (898 / 755 / 701)
+  //   1024, 8 (8.5, 2.3) 1463 / 1317 / 1290 (1466 / 1174 / 1060)
+  //   1024, 32 (34, 9.0) 5194 / 4494 / 4110 (5193 / 3921 / 3884)
+  // So 64 x 64 tiles from 5/4 per unit on, and whole ones from two per unit on or
+  // where their one or two rounds are 85 % full. A side that ends in half a tile
+  // loses up to 3 % to the 64 x 64 ones (960, 32: 3145 against 3072).
+  // (The sides of one problem have 1.1 tiles of 64 x 64 per unit at most; a side of
+  // more than kSmallGram columns has tiles of its own and does not count.)
+  int whole = 0;
+  if (tab && whole_sides(f.m, f.n)) {
+    const int sides = whole_sides(f.m, f.n);
+    const int64_t n = problems * gram_plan(f.m, f.n, sides, 1, f.cus).G, rounds = (n + f.cus - 1) / f.cus;
+    if (n >= 2 * f.cus || 100 * n >= 85 * rounds * f.cus) whole = fast = sides;
+  }
+  int64_t tiles = 0;  // of 64 x 64
   for (int sd = 0; sd < 2; ++sd)
-    if (a.s[sd].d <= kSmallGram) tiles += (int64_t)(tab ? count : 1) * (a.s[sd].nb * (a.s[sd].nb + 1) / 2);
+    if (a.s[sd].d <= kSmallGram && !(fast & (1 << sd)))
+      tiles += problems * (a.s[sd].nb * (a.s[sd].nb + 1) / 2);
   const bool many = 4 * tiles >= 5 * (int64_t)f.cus;
   int small = 0, slow = 0, nprep = 0, nslow = 0, nsmall = 0;
   for (int sd = 0; sd < 2; ++sd) {
-    const int d = a.s[sd].d, nb = a.s[sd].nb;
-    if (d <= kSmallGram && !many) {
+    const int nb = a.s[sd].nb;
+    if (fast & (1 << sd)) {
+      nprep += nb * nb;
+    } else if (!many) {
       small |= 1 << sd;
       nsmall += nb * (2 * nb + 1);
-    } else if (fast & (1 << sd)) {
-      nprep += nb * nb;
     } else {
       slow |= 1 << sd;
       nslow += nb * (nb + 1) / 2;
@@ -1805,7 +1856,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
     });
   }
   if (fast) {
-    const GramPlan pl = gram_plan(f.m, f.n, fast, f.cus);
+    const GramPlan pl = gram_plan(f.m, f.n, fast, whole, f.cus);
     go(nprep, s, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
       constexpr bool BT = decltype(bat)::value;
       if (dt == GPTQ2D_F32)
@@ -1823,7 +1874,7 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
       constexpr bool BT = decltype(bat)::value;
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gram128<BT>), g, dim3(NT), 0, st, a, pl, f.gpart, bc);
     });
-    go(pl.G - 1, s, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
+    go(whole ? 0 : pl.G - 1, s, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t st) {
       constexpr bool BT = decltype(bat)::value;
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gram_fix<BT>), g, dim3(NT), 0, st, a, pl,
                          (const double*)f.gpart, bc);

@@ -51,6 +51,36 @@ def test_batch_routes_same_bits(m, n, count):
             assert torch.equal(x, y), f"problem {p}"
 
 
+# tiles of 64 x 64 and of 128 x 128 fill 256 compute units from 5/4 and from 0.85 per
+# unit (one or two rounds) or two per unit on: Grams on 64 x 64 tiles, ragged and
+# whole; on whole 128 x 128 tiles, one side or both, a round and more
+@pytest.mark.parametrize("m,n,count", [(512, 384, 6), (700, 321, 4), (130, 70, 60), (1024, 896, 4), (640, 512, 9),
+                                       (768, 200, 26), (64, 1024, 16)])
+@pytest.mark.parametrize("kind", ["upper", "lower", "blocks"])
+@pytest.mark.parametrize("dtype,reverse", [(torch.float32, False), (torch.float32, True), (torch.float64, True)])
+def test_batch_gram_routes_same_bits(m, n, count, kind, dtype, reverse):
+    """Bases with zero blocks, which the larger tiles skip, in both types and orders."""
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+
+    def basis(d):
+        t = torch.randn(d, d, generator=g, device="cuda", dtype=torch.float64) / d ** 0.5
+        if kind == "blocks":
+            at = torch.arange(d, device="cuda") // 100
+            t *= at.unsqueeze(0) == at.unsqueeze(1)
+        else:
+            t = t.triu_() if kind == "upper" else t.tril_()
+        t.diagonal().add_(2.0)
+        return t.to(dtype)
+    As, Bs = [basis(m) for _ in range(count)], [basis(n) for _ in range(count)]
+    fs = [binding.Factors(m, n, reverse=reverse) for _ in range(count)]
+    binding.factor_batched(fs, As, Bs)
+    one = binding.Factors(m, n, reverse=reverse)
+    for p in (0, count // 2, count - 1):
+        one.compute(As[p], Bs[p])
+        for x, y in zip(one.export(), fs[p].export()):
+            assert torch.equal(x, y), f"problem {p}"
+
+
 def test_small_side_beside_a_large_one():
     """Each side's Gram takes the route of its own size: the factors of a 200 side
     do not depend on the other side, but for the order of the panels' sums."""
