@@ -41,8 +41,6 @@ static void free_all(Factors* f) {
   if (f->own) (void)hipStreamDestroy(f->own);
   f->ev_near = f->ev_far = f->ev_far1 = f->ev_own = nullptr;
   f->aux = f->own = nullptr;
-  free_schedule(f->sched);
-  if (!f->bshared) free_schedule(f->bsched);
 }
 
 static gptq2d_status alloc(Factors* f, void** p, size_t bytes) {
@@ -175,14 +173,7 @@ gptq2d_status gptq2d_factors_create(int m, int n, gptq2d_factors_t* out) {
     // order of the sources either way: the same bits.
     const int wide = std::max(f->MT, f->NT) > 64 ? 5 : 4;
     const int g = per_launch <= 640 ? 2 : per_launch <= 1280 ? 3 : wide;
-    const int gs = env_int("GPTQ2D_BATCH", g), gb = env_int("GPTQ2D_BATCH", wide);
-    st = build_schedule(*f, gs, f->sched);
-    if (st == GPTQ2D_OK && gb == gs) {
-      f->bsched = f->sched;
-      f->bshared = true;
-    } else if (st == GPTQ2D_OK) {
-      st = build_schedule(*f, gb, f->bsched);
-    }
+    st = build_schedules(*f, env_int("GPTQ2D_BATCH", g), env_int("GPTQ2D_BATCH", wide));
   }
   if (st != GPTQ2D_OK) {
     free_all(f);

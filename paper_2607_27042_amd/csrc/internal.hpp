@@ -17,7 +17,6 @@ namespace g2d {
 // (cols - 1) << 3, y = first target tile row, z = first target tile column,
 // w = first source | (one past last source) << 16.
 struct Schedule {
-  int g = 0;                     // batch width in tile anti-diagonals
   int stages = 0;                // tile anti-diagonals: MT + NT - 1
   std::vector<int> offset;       // per stage: first task (size stages + 1)
   std::vector<int> bin_offset;   // per stage: first bin (size stages + 1)
@@ -25,7 +24,6 @@ struct Schedule {
   int4* d_bins = nullptr;        // {first task in the stage, counts by shape}, grouped by stage
   int4* d_stage = nullptr;       // per stage: {offset, bin_offset, bins, 0} (batched rounding)
   void* d_base = nullptr;        // the handle's fixed stage arguments on the device (batched rounding)
-  size_t ntasks = 0;
 };
 
 struct Factors {
@@ -58,8 +56,7 @@ struct Factors {
   hipStream_t own = nullptr;
   hipEvent_t ev_own = nullptr;
   Schedule sched;   // delivery plan of a round by itself
-  Schedule bsched;  // and in a batch (sched's device arrays where bshared)
-  bool bshared = false;
+  Schedule bsched;  // and in a batch (the same device arrays where the plans are equal)
   // launch timing of the sweep's stage kernel (diagnostics): while enabled,
   // every stage launch records its start and end time stamps into a pair of
   // events; the pairs accumulate until they are read
@@ -147,8 +144,8 @@ void schedule_tasks(int MT, int NT, int g, std::vector<int4>& all, std::vector<i
 gptq2d_status pack_bins(int MT, int NT, int units, std::vector<int4>& all,
                         const std::vector<int>& offset, std::vector<int4>& bins,
                         std::vector<int>& bin_offset);
-gptq2d_status build_schedule(Factors& f, int g, Schedule& sched);
-void free_schedule(Schedule& s);
+// The handle's delivery plans: batch width g for a round by itself, gbatch in a batch.
+gptq2d_status build_schedules(Factors& f, int g, int gbatch);
 // allow_timing = false: no stage-launch timing even if the handle asks for it
 // (timing creates HIP events on first use)
 gptq2d_status launch_round(const Factors& f, gptq2d_dtype dt, const void* X, int64_t ldx,

@@ -1019,15 +1019,31 @@ Workspace workspace_carve(const Factors& f, void* base) {
 // Task word: x = dir | overwrite << 1 | (rows - 1) << 2 | (cols - 1) << 3
 // (rows, cols in tiles), y = first target tile row, z = first target tile
 // column, w = first source | (one past the last source) << 16.
+// (creating a handle waits for this: stable counting sorts instead of comparisons)
+
+// Stable order of the items by key (0 <= key < n), and each key's first place.
+static void counting_order(const std::vector<int>& key, int n, std::vector<int>& order, std::vector<int>& at) {
+  at.assign(n + 1, 0);
+  for (int k : key) ++at[k + 1];
+  for (int k = 0; k < n; ++k) at[k + 1] += at[k];
+  order.resize(key.size());
+  std::vector<int> next(at);
+  for (size_t i = 0; i < key.size(); ++i) order[next[key[i]]++] = (int)i;
+}
+
 void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<int>& off) {
   const int S = MT + NTt - 1;
-  if (g < 1) g = 1;
-  std::vector<std::vector<int4>> per(S);
+  g = std::max(1, std::min(g, std::max(MT, NTt)));  // (wider ones are the same)
+  std::vector<int4> found;
+  std::vector<int> key;  // of the task: work, launch
   std::vector<double> load(S, 0.0);
-  auto work = [](int nr, int nc, int k) { return (double)nr * nc * k; };  // in 64^3 units
+  auto work = [](int nr, int nc, int k) { return nr * nc * k; };  // in 64^3 units
+  const int wmax = 4 * std::max(g, 2);
   auto emit = [&](int launch, int dir, int ti, int tj, int nr, int nc, int s0, int s1) {
-    per[launch].push_back(make_int4(dir | ((nr - 1) << 2) | ((nc - 1) << 3), ti, tj, s0 | (s1 << 16)));
-    load[launch] += work(nr, nc, s1 - s0);
+    const int w = work(nr, nc, s1 - s0);
+    found.push_back(make_int4(dir | ((nr - 1) << 2) | ((nc - 1) << 3), ti, tj, s0 | (s1 << 16)));
+    key.push_back(launch * wmax + (wmax - w));
+    load[launch] += w;
   };
   struct Batch {
     int release, deadline, slot, dir, r0, c0, nr, nc, s0, s1;
@@ -1082,56 +1098,52 @@ void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<
   // middle launches are bound by the deliveries that are due there, and the
   // early ones take more of them.
   const double per_unit = std::max(MT, NTt) > 64 ? 20.0 : 16.0;
-  std::vector<std::vector<int>> released(S);
-  for (int i = 0; i < (int)batches.size(); ++i) released[batches[i].release].push_back(i);
-  auto later = [&](int x, int y) {
-    return batches[x].deadline != batches[y].deadline ? batches[x].deadline > batches[y].deadline : x > y;
+  // A super-tile and direction has its batches in the order of their deadlines, and
+  // one per launch: only its first one left waits for room. come[k]: the slots whose
+  // next batch can go from launch k on (a list through slot_next).
+  std::vector<int> come(S + 1, -1), slot_next(nslot);
+  auto arrive = [&](int i, int k) {
+    slot_next[batches[i].slot] = come[std::min(k, S)];
+    come[std::min(k, S)] = i;
   };
-  std::priority_queue<int, std::vector<int>, decltype(later)> avail(later);
-  std::vector<int> slot_at(nslot, -1);
+  for (int i = 0; i < (int)batches.size(); ++i)
+    if (i == 0 || batches[i].slot != batches[i - 1].slot) arrive(i, batches[i].release);
+  // earliest deadline first, then the batch found first
+  std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> avail;
   for (int k = 0; k < S; ++k) {
-    for (int i : released[k]) avail.push(i);
+    for (int i = come[k]; i >= 0; i = slot_next[batches[i].slot])
+      avail.push((int64_t)batches[i].deadline << 32 | i);
     const int nsweep = std::min(k, MT - 1) - std::max(0, k - NTt + 1) + 1;
     const double room = per_unit * std::max(0, 256 - nsweep);
-    std::vector<int> held;
     while (!avail.empty()) {
-      const int i = avail.top();
-      const Batch& bt = batches[i];
-      const bool due = bt.deadline <= k;
+      const int64_t top = avail.top();
+      const bool due = (top >> 32) <= k;
       if (!due && load[k] >= room) break;
       avail.pop();
-      if (slot_at[bt.slot] == k) {  // this super-tile already has a delivery here
-        held.push_back(i);
-        continue;
-      }
-      slot_at[bt.slot] = k;
+      const int i = (int)(uint32_t)top;
+      const Batch& bt = batches[i];
       emit(k, bt.dir, bt.r0, bt.c0, bt.nr, bt.nc, bt.s0, bt.s1);
+      if (i + 1 < (int)batches.size() && batches[i + 1].slot == bt.slot)
+        arrive(i + 1, std::max(k + 1, batches[i + 1].release));
     }
-    for (int i : held) avail.push(i);
   }
   // overwrite flag: the first delivery in launch order into each target
   std::vector<char> seen((size_t)2 * MT * NTt, 0);
-  all.clear();
-  off.assign(S + 1, 0);
-  for (int k = 0; k < S; ++k) {
-    // biggest products first, so the short ones fill in behind them
-    std::stable_sort(per[k].begin(), per[k].end(), [](const int4& x, const int4& y) {
-      const int wx = ((x.w >> 16) - (x.w & 0xffff)) * (((x.x >> 2) & 1) + 1) * (((x.x >> 3) & 1) + 1);
-      const int wy = ((y.w >> 16) - (y.w & 0xffff)) * (((y.x >> 2) & 1) + 1) * (((y.x >> 3) & 1) + 1);
-      return wx > wy;
-    });
-    for (int4& tk : per[k]) {
-      const int dir = tk.x & 1;
-      char& f = seen[2 * ((size_t)tk.y * NTt + tk.z) + dir];
-      if (!f) tk.x |= 2;
-      const int nr = ((tk.x >> 2) & 1) + 1, nc = ((tk.x >> 3) & 1) + 1;
-      for (int r = 0; r < nr; ++r)
-        for (int c = 0; c < nc; ++c) seen[2 * ((size_t)(tk.y + r) * NTt + tk.z + c) + dir] = 1;
-    }
-    off[k] = (int)all.size();
-    all.insert(all.end(), per[k].begin(), per[k].end());
+  // launch by launch, biggest products first, so the short ones fill in behind them
+  std::vector<int> order, at;
+  counting_order(key, S * wmax, order, at);
+  all.resize(found.size());
+  for (size_t i = 0; i < order.size(); ++i) {
+    int4& tk = all[i] = found[order[i]];
+    const int dir = tk.x & 1;
+    char& f = seen[2 * ((size_t)tk.y * NTt + tk.z) + dir];
+    if (!f) tk.x |= 2;
+    const int nr = ((tk.x >> 2) & 1) + 1, nc = ((tk.x >> 3) & 1) + 1;
+    for (int r = 0; r < nr; ++r)
+      for (int c = 0; c < nc; ++c) seen[2 * ((size_t)(tk.y + r) * NTt + tk.z + c) + dir] = 1;
   }
-  off[S] = (int)all.size();
+  off.resize(S + 1);
+  for (int k = 0; k <= S; ++k) off[k] = at[k * wmax];
 }
 
 // Bins of a stage: one per compute unit, filled longest-processing-time
@@ -1156,55 +1168,76 @@ gptq2d_status pack_bins(int MT, int NTt, int units, std::vector<int4>& all,
   boff.assign(S + 1, 0);
   std::vector<int4> out;
   out.reserve(all.size());
-  auto cost = [](const int4& x) {
-    const int K = (x.w >> 16) - (x.w & 0xffff);
-    const int tiles = (((x.x >> 2) & 1) + 1) * (((x.x >> 3) & 1) + 1);
-    const double chunk = tiles == 4 ? kChunk4 : tiles == 2 ? kChunk2 : kChunk1;
-    return ((x.x >> 1) & 1 ? kStartOw : kStartAdd) + chunk * (TB / KQ) * K;
+  auto shape = [](const int4& x) { return 3 - ((x.x >> 2) & 1) * 2 - ((x.x >> 3) & 1); };  // 2 x 2, 2 x 1, 1 x 2, 1 x 1
+  auto depth = [](const int4& x) { return (x.w >> 16) - (x.w & 0xffff); };
+  auto cost = [](int sh, int K, int ow) {
+    const double chunk = sh == 0 ? kChunk4 : sh == 3 ? kChunk1 : kChunk2;
+    return (ow ? kStartOw : kStartAdd) + chunk * (TB / KQ) * K;
   };
+  // the kinds of tasks (depth, shape, overwrite) by falling cost, equal costs together
+  int kmax = 0;
+  for (const int4& x : all) kmax = std::max(kmax, depth(x));
+  auto kind = [&](const int4& x) { return (depth(x) * 4 + shape(x)) * 2 + ((x.x >> 1) & 1); };
+  const int kinds = 8 * (kmax + 1);
+  std::vector<double> kcost(kinds);
+  std::vector<int> by(kinds), rank(kinds);
+  for (int q = 0; q < kinds; ++q) {
+    kcost[q] = cost((q >> 1) & 3, q >> 3, q & 1);
+    by[q] = q;
+  }
+  std::sort(by.begin(), by.end(), [&](int x, int y) { return kcost[x] > kcost[y]; });
+  for (int x = 0; x < kinds; ++x) rank[by[x]] = x > 0 && kcost[by[x]] == kcost[by[x - 1]] ? rank[by[x - 1]] : x;
   const int nb = std::max(1, units);
-  std::vector<std::vector<int>> member(nb);  // (kept between stages: no allocations in the loop)
-  std::vector<int> order;
-  std::vector<double> costs(all.size());
-  for (size_t i = 0; i < all.size(); ++i) costs[i] = cost(all[i]);
+  std::vector<int> key, order, at, home;
+  typedef std::pair<double, int> Load;
+  std::vector<Load> heap;
   for (int k = 0; k < S; ++k) {
     boff[k] = (int)bins.size();
     const int n = off[k + 1] - off[k];
     if (n == 0) continue;
+    const int4* tk = all.data() + off[k];
     const int nsweep = std::min(k, MT - 1) - std::max(0, k - NTt + 1) + 1;
     const int nfree = std::max(0, units - nsweep);
-    order.resize(n);
-    for (int i = 0; i < n; ++i) order[i] = off[k] + i;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return costs[x] > costs[y]; });
-    for (auto& m : member) m.clear();
-    // least-loaded bin first (ties: lowest index)
-    typedef std::pair<double, int> Load;
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-    for (int b = 0; b < nb; ++b) heap.push(Load(b < nfree ? 0.0 : kSweepCost, b));
-    for (int i : order) {
-      Load top = heap.top();
-      heap.pop();
-      member[top.second].push_back(i);
-      top.first += costs[i];
-      heap.push(top);
+    key.resize(n);
+    home.resize(n);
+    for (int i = 0; i < n; ++i) key[i] = rank[kind(tk[i])];
+    counting_order(key, kinds, order, at);
+    if (n <= nfree) {  // an empty bin for each
+      for (int i = 0; i < n; ++i) home[order[i]] = i;
+    } else {
+      // least-loaded bin first (ties: lowest index)
+      heap.clear();
+      for (int b = 0; b < nb; ++b) heap.emplace_back(b < nfree ? 0.0 : kSweepCost, b);  // (in heap order)
+      for (int i : order) {
+        home[i] = heap[0].second;
+        const Load top(heap[0].first + kcost[kind(tk[i])], heap[0].second);
+        int p = 0;
+        for (int c = 1; c < nb; c = 2 * p + 1) {
+          if (c + 1 < nb && heap[c + 1] < heap[c]) ++c;
+          if (top < heap[c]) break;
+          heap[p] = heap[c];
+          p = c;
+        }
+        heap[p] = top;
+      }
     }
+    // bin by bin, grouped by target shape, in the order they were taken
+    key.clear();
+    for (int i : order) key.push_back(home[i] * 4 + shape(tk[i]));
+    std::vector<int>& taken = home;
+    taken.swap(order);
+    counting_order(key, 4 * nb, order, at);
     const int base = (int)out.size();
+    for (int x : order) out.push_back(tk[taken[x]]);
     for (int b = 0; b < nb; ++b) {
-      if (member[b].empty()) continue;
-      // grouped by target shape: 2 x 2, 2 x 1, 1 x 2, 1 x 1
-      if (member[b].size() > 0xffff) {
+      const int* c = &at[4 * b];
+      if (c[4] == c[0]) continue;
+      if (c[4] - c[0] > 0xffff) {
         set_error("delivery plan: too many products in one bin");
         return GPTQ2D_ERR_INVALID_ARG;
       }
-      int cnt[4] = {0, 0, 0, 0};
-      const int first = (int)out.size() - base;
-      for (int g = 0; g < 4; ++g)
-        for (int i : member[b]) {
-          const int nr = ((all[i].x >> 2) & 1) + 1, nc = ((all[i].x >> 3) & 1) + 1;
-          const int sh = nr == 2 ? (nc == 2 ? 0 : 1) : (nc == 2 ? 2 : 3);
-          if (sh == g) out.push_back(all[i]), ++cnt[g];
-        }
-      bins.push_back(make_int4(first, cnt[0] | (cnt[1] << 16), cnt[2] | (cnt[3] << 16), 0));
+      bins.push_back(make_int4((int)out.size() - base - n + c[0], (c[1] - c[0]) | ((c[2] - c[1]) << 16),
+                               (c[3] - c[2]) | ((c[4] - c[3]) << 16), 0));
     }
   }
   boff[S] = (int)bins.size();
@@ -1212,49 +1245,47 @@ gptq2d_status pack_bins(int MT, int NTt, int units, std::vector<int4>& all,
   return GPTQ2D_OK;
 }
 
-void free_schedule(Schedule& sc) {
-  if (sc.d_tasks) (void)hipFree(sc.d_tasks);
-  if (sc.d_bins) (void)hipFree(sc.d_bins);
-  if (sc.d_stage) (void)hipFree(sc.d_stage);
-  if (sc.d_base) (void)hipFree(sc.d_base);
-  sc.d_tasks = nullptr;
-  sc.d_bins = nullptr;
-  sc.d_stage = nullptr;
-  sc.d_base = nullptr;
-}
-
-gptq2d_status build_schedule(Factors& f, int g, Schedule& sched) {
-  std::vector<int4> all;
-  std::vector<int> off;
-  if (g < 1) g = 1;
-  schedule_tasks(f.MT, f.NT, g, all, off);
+// Both plans in one allocation and one upload (each costs the creation of a handle
+// 10 to 20 us), and one plan where they are the same.
+gptq2d_status build_schedules(Factors& f, int g, int gbatch) {
   int units = 0;
   if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, f.device) != hipSuccess ||
       units <= 0)
     units = 256;
-  std::vector<int4> bins;
-  std::vector<int> boff;
-  const gptq2d_status st = pack_bins(f.MT, f.NT, units, all, off, bins, boff);
-  if (st != GPTQ2D_OK) return st;
-  free_schedule(sched);
-  if (!all.empty()) {
-    hipError_t e = hipMalloc(&sched.d_tasks, all.size() * sizeof(int4));
-    if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(sched.d_tasks, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "schedule upload");
-    e = hipMalloc(&sched.d_bins, bins.size() * sizeof(int4));
-    if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(sched.d_bins, bins.data(), bins.size() * sizeof(int4), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "schedule upload");
+  const int S = f.MT + f.NT - 1;
+  std::vector<int4> all[2], bins[2];
+  schedule_tasks(f.MT, f.NT, std::max(g, 1), all[0], f.sched.offset);
+  if (gbatch != g) schedule_tasks(f.MT, f.NT, std::max(gbatch, 1), all[1], f.bsched.offset);
+  const bool same = gbatch == g || (f.sched.offset == f.bsched.offset &&
+                                    !memcmp(all[0].data(), all[1].data(), all[0].size() * sizeof(int4)));
+  const int plans = same ? 1 : 2;
+  Schedule* const sc[2] = {&f.sched, &f.bsched};
+  size_t at[2] = {0, 0}, total = 0;  // in int4s: tasks, bins, stage table, stage arguments
+  for (int p = 0; p < plans; ++p) {
+    const gptq2d_status st = pack_bins(f.MT, f.NT, units, all[p], sc[p]->offset, bins[p], sc[p]->bin_offset);
+    if (st != GPTQ2D_OK) return st;
+    at[p] = total;
+    total += all[p].size() + bins[p].size() + S + (sizeof(StageArgs) + sizeof(int4) - 1) / sizeof(int4);
   }
-  {
-    const int S = f.MT + f.NT - 1;
-    std::vector<int4> stab(S);
-    for (int k = 0; k < S; ++k) stab[k] = int4{off[k], boff[k], boff[k + 1] - boff[k], 0};
-    hipError_t e = hipMalloc(&sched.d_stage, S * sizeof(int4));
-    if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(sched.d_stage, stab.data(), S * sizeof(int4), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "schedule upload");
+  void* block = nullptr;
+  hipError_t e = hipMalloc(&block, total * sizeof(int4));
+  if (e != hipSuccess) return hip_fail(e, "schedule allocation");
+  f.allocations.push_back(block);
+  std::vector<int4> image(total);
+  for (int p = 0; p < plans; ++p) {
+    Schedule& q = *sc[p];
+    int4* const dev = (int4*)block + at[p];
+    const size_t nt = all[p].size(), nbins = bins[p].size();
+    q.stages = S;
+    q.d_tasks = nt ? dev : nullptr;
+    q.d_bins = nt ? dev + nt : nullptr;
+    q.d_stage = dev + nt + nbins;
+    q.d_base = dev + nt + nbins + S;
+    int4* const h = image.data() + at[p];
+    std::copy(all[p].begin(), all[p].end(), h);
+    std::copy(bins[p].begin(), bins[p].end(), h + nt);
+    for (int k = 0; k < S; ++k)
+      h[nt + nbins + k] = int4{q.offset[k], q.bin_offset[k], q.bin_offset[k + 1] - q.bin_offset[k], 0};
     // the fixed stage arguments of the handle (batched rounding)
     StageArgs b{};
     b.m = f.m;
@@ -1267,19 +1298,14 @@ gptq2d_status build_schedule(Factors& f, int g, Schedule& sched) {
     b.U = f.U;
     b.dL = f.dL;
     b.dU = f.dU;
-    b.tasks = sched.d_tasks;
-    b.bins = sched.d_bins;
-    b.stab = sched.d_stage;
-    e = hipMalloc(&sched.d_base, sizeof(StageArgs));
-    if (e != hipSuccess) return hip_fail(e, "schedule allocation");
-    e = hipMemcpy(sched.d_base, &b, sizeof(StageArgs), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "schedule upload");
+    b.tasks = q.d_tasks;
+    b.bins = q.d_bins;
+    b.stab = q.d_stage;
+    memcpy(h + nt + nbins + S, &b, sizeof(b));
   }
-  sched.g = g;
-  sched.stages = f.MT + f.NT - 1;
-  sched.offset = off;
-  sched.bin_offset = boff;
-  sched.ntasks = all.size();
+  e = hipMemcpy(block, image.data(), total * sizeof(int4), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "schedule upload");
+  if (same) f.bsched = f.sched;
   return GPTQ2D_OK;
 }
 

@@ -2,6 +2,7 @@
 point, validates arguments without touching a device, and its host-side
 delivery plan is a partition of the deferred feedback."""
 import ctypes
+import hashlib
 import itertools
 
 import numpy as np
@@ -59,6 +60,20 @@ def test_null_handle_is_rejected(lib):
     assert lib.gptq2d_factors_create(0, 5, ctypes.byref(out)) == -1
     assert lib.gptq2d_factors_create(5, 70000, ctypes.byref(out)) == -1
     lib.gptq2d_factors_destroy(null)
+
+
+# the plans' tasks and offsets as they were built with comparison sorts and a queue of
+# every batch: which deliveries share a launch, and in what order, decides a round's time
+PLANS = {(65, 1, 2): "15ec7bf0b50732b4", (200, 120, 4): "c9df6c1df8011c1e", (512, 384, 2): "b7bfe3d5230b27ea",
+         (1000, 700, 3): "070350a14b2f8e78", (2112, 1984, 1): "9435510b28c0f573", (64, 9000, 2): "758650a007dca9b9",
+         (3000, 2000, 3): "cb3eb9257113543c", (4160, 2560, 5): "e2a3d3913f28adc1",
+         (700, 900, 2 ** 31 - 1): "a5a1ef0d9c1327ae"}
+
+
+@pytest.mark.parametrize("m,n,g", list(PLANS))
+def test_schedule_is_the_same_plan(m, n, g):
+    tasks, offs = binding.gptq2d_schedule_tasks(m, n, g)
+    assert hashlib.sha256(tasks.tobytes() + offs.tobytes()).hexdigest()[:16] == PLANS[m, n, g]
 
 
 def _task_fields(x):
