@@ -123,10 +123,10 @@ gptq2d_status gptq2d_factors_create(int m, int n, gptq2d_factors_t* out) {
   A(&f->dL, mp);
   A(&f->dU, np);
   A(&f->gram[0], mp * mp);
-  A(&f->inv[0], mp * mp);
+  A(&f->inv[0], gram_panel_rows(m) * mp);
   A(&f->dinv[0], mp * TB);
   A(&f->gram[1], np * np);
-  A(&f->inv[1], np * np);
+  A(&f->inv[1], gram_panel_rows(n) * np);
   A(&f->dinv[1], np * TB);
   if (hipDeviceGetAttribute(&f->cus, hipDeviceAttributeMultiprocessorCount, f->device) != hipSuccess ||
       f->cus <= 0)

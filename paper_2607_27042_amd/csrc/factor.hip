@@ -509,19 +509,18 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
 }
 
 // (i0, i1 select the part i0 <= i < i1 of the loads)
-// rp, rq: the rows the two panels have (64 in the last, half row block: its
-// other loads repeat a valid row and are not used)
-__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int rp, int rq, int c,
-                                           GramChunk& g, int w, int l, int i0 = 0, int i1 = 8) {
+// (a last, half row block is followed by 64 rows of the buffer that nobody has
+// written; what comes of them is not stored)
+__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int c, GramChunk& g, int w, int l, int i0 = 0, int i1 = 8) {
   typedef __attribute__((address_space(3))) void lds_v;
   const int ar = l >> 4, ap = (l & 15) ^ ar;
   const int64_t k0 = (int64_t)c * GQ + 2 * ap;
 #pragma unroll
   for (int i = i0; i < i1; ++i) {
     const int j = w + 4 * i;
-    const int row = 4 * j + ar;
-    __builtin_amdgcn_global_load_lds((const void*)(Sp + (int64_t)min(row, rp - 1) * ld + k0), (lds_v*)&g.a[j][0], 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((const void*)(Sq + (int64_t)min(row, rq - 1) * ld + k0), (lds_v*)&g.b[j][0], 16, 0, 0);
+    const int64_t ro = (int64_t)(4 * j + ar) * ld + k0;
+    __builtin_amdgcn_global_load_lds((const void*)(Sp + ro), (lds_v*)&g.a[j][0], 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(Sq + ro), (lds_v*)&g.b[j][0], 16, 0, 0);
   }
 }
 
@@ -605,7 +604,7 @@ __global__ __launch_bounds__(PLT) void k_gram_plan(FacArgs f0, GramPlan pl, Batc
 // Chunks c0 .. c1-1 of the tile (bp, bq) of one side into acc (zeroed here).
 __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0, int c1, GramChunk* buf,
                                           d4 (&acc)[4][4]) {
-  const int d = sd.dp, rp = min(128, d - 128 * bp), rq = min(128, d - 128 * bq);
+  const int d = sd.dp;
   const double* Sp = sd.li + (int64_t)(128 * bp) * d;
   const double* Sq = sd.li + (int64_t)(128 * bq) * d;
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
@@ -614,7 +613,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  if (c0 < c1) gram_issue(Sp, Sq, d, rp, rq, c0, buf[0], w, l);
+  if (c0 < c1) gram_issue(Sp, Sq, d, c0, buf[0], w, l);
   for (int c = c0; c < c1; ++c) {
     const int cb = (c - c0) & 1;
     // the next chunk's loads in two halves, the second half-way through this
@@ -622,7 +621,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
     // pipeline takes it)
     const bool more = c + 1 < c1;
     if (more) {
-      gram_issue(Sp, Sq, d, rp, rq, c + 1, buf[cb ^ 1], w, l, 0, 4);
+      gram_issue(Sp, Sq, d, c + 1, buf[cb ^ 1], w, l, 0, 4);
       __builtin_amdgcn_s_waitcnt(0x0f78);  // vmcnt(8): chunk c has landed
     } else {
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -644,7 +643,7 @@ __device__ __forceinline__ void gram_part(const Side& sd, int bp, int bq, int c0
       const int cur = kk & 1, nx = cur ^ 1;
       if (kk == GQ / 8 && more) {
         __builtin_amdgcn_sched_barrier(0);
-        gram_issue(Sp, Sq, d, rp, rq, c + 1, buf[cb ^ 1], w, l, 4, 8);
+        gram_issue(Sp, Sq, d, c + 1, buf[cb ^ 1], w, l, 4, 8);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (kk + 1 < GQ / 4) {
@@ -833,6 +832,12 @@ static int sides_over(int d, int m, int n) { return (m > d ? 1 : 0) | (n > d ? 2
 static int fast_sides(int m, int n) { return sides_over(kSmallGram, m, n); }
 static int whole_sides(int m, int n) {
   return fast_sides(m, n) ? 0 : sides_over(kWholeGram, m % 128 ? 0 : m, n % 128 ? 0 : n);
+}
+
+// Rows of a side's panel: whole 128-row blocks where the 128 x 128 tiles read them.
+size_t gram_panel_rows(int d) {
+  const int a = d > kSmallGram ? 128 : TB;
+  return (size_t)(d + a - 1) / a * a;
 }
 
 size_t gram_part_doubles(int m, int n, int cus) {
@@ -1247,14 +1252,19 @@ __device__ __forceinline__ void upd_counts(const Side& sd, const UpdRange& r, in
 
 // acc += sum over 64-deep blocks b of A_b op(B_b), A_b at pa + b*sa_, B_b at
 // pb + b*sb_; BT: B given transposed. Double-buffered through LDS.
-// each: old -= the sum so far after every block but the last, the sum starts again.
+// old: set to the values at po, whose loads go out behind the first operands'; each:
+// old -= the sum so far after every block but the last, the sum starts again.
 template <int BT>
 __device__ void gemm_blocks(Acc& acc, const double* pa, int64_t lda, int64_t sa_, const double* pb,
                             int64_t ldb, int64_t sb_, int nb, Stage64* st, Acc* old = nullptr,
-                            bool each = false) {
+                            const double* po = nullptr, int64_t ldo = 0, bool each = false) {
   double ra[16], rb[16];
   load_blk(pa, lda, ra);
   load_blk(pb, ldb, rb);
+  if (old) {
+    old->zero();
+    acc_add_from(*old, po, ldo);
+  }
   for (int b = 0; b < nb; ++b) {
     Stage64& s = st[b & 1];
     put_a(s, ra);
@@ -1310,9 +1320,7 @@ __global__ __launch_bounds__(NT) void k_update(FacArgs f0, UpdRange r, BatchCtx 
     const double* pa = sd.gr + (int64_t)bi * TB * sd.dp + (int64_t)r.k0 * TB;
     const double* pb = sd.gr + (int64_t)bj * TB * sd.dp + (int64_t)r.k0 * TB;
     Acc old;
-    old.zero();
-    acc_add_from(old, out, sd.dp);
-    gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st, &old, r.each);
+    gemm_blocks<1>(acc, pa, sd.dp, TB, pb, sd.dp, TB, k1 - r.k0, st, &old, out, sd.dp, r.each);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc.t[i] = old.t[i] - acc.t[i];
     if (bi == r.dg && bj == r.dg) {

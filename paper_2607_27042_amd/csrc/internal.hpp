@@ -116,6 +116,8 @@ gptq2d_status check_round_args(const Factors* f, gptq2d_dtype dt, const void* X,
 // factorisation launches (enqueued on stream, no synchronisation)
 // doubles of scratch for the Gram tiles split between work groups
 size_t gram_part_doubles(int m, int n, int cus);
+// rows of a side's inverse buffer, which holds the Gram's panel first
+size_t gram_panel_rows(int d);
 size_t gram_env_ints(int m, int n);
 // stream-ordered upload of host words into device memory (bytes and dst
 // multiples of 8; the host buffer may be reused on return)
