@@ -827,11 +827,18 @@ constexpr int kSmallGram = 1024;
 // In a batch, sides of whole 128 x 128 tiles over 448 take them where they fill the
 // device (factor_impl has the measurements).
 constexpr int kWholeGram = 448;
+// Beside a larger side, a side of whole 128 x 128 tiles over 896 shares that one's
+// launches, in one problem and in a batch (with / without: 8192 x 1024 13.40 / 13.49
+// ms, 1024 x 4096 3005 / 3040 us, 1024 x 1536 852 / 885, 4 problems of 1024 x 2048
+// 1820 / 1882). Batches of smaller ones can lose by the longer launch: 4 of 896 x 1280
+// 1175 / 1067, 8 of 640 x 1536 1731 / 1579, against 1409 / 1435 for 2 of 896 x 2048.
+constexpr int kBesideLarge = 896;
 
 static int sides_over(int d, int m, int n) { return (m > d ? 1 : 0) | (n > d ? 2 : 0); }
-static int fast_sides(int m, int n) { return sides_over(kSmallGram, m, n); }
-static int whole_sides(int m, int n) {
-  return fast_sides(m, n) ? 0 : sides_over(kWholeGram, m % 128 ? 0 : m, n % 128 ? 0 : n);
+static int whole_sides(int d, int m, int n) { return sides_over(d, m % 128 ? 0 : m, n % 128 ? 0 : n); }
+static int fast_sides(int m, int n) {
+  const int large = sides_over(kSmallGram, m, n);
+  return large ? large | whole_sides(kBesideLarge, m, n) : 0;
 }
 
 // Rows of a side's panel: whole 128-row blocks where the 128 x 128 tiles read them.
@@ -848,7 +855,8 @@ size_t gram_part_doubles(int m, int n, int cus) {
 }
 
 size_t gram_env_ints(int m, int n) {
-  const int fast = fast_sides(m, n) | whole_sides(m, n);
+  int fast = fast_sides(m, n);
+  if (!fast) fast = whole_sides(kWholeGram, m, n);
   if (!fast) return 0;
   const GramPlan pl = gram_plan(m, n, fast, 0, 1);
   return gram_view_ints(pl.n0, pl.n1, pl.t0 + pl.t1);
@@ -1829,8 +1837,8 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   // (The sides of one problem have 1.1 tiles of 64 x 64 per unit at most; a side of
   // more than kSmallGram columns has tiles of its own and does not count.)
   int whole = 0;
-  if (tab && whole_sides(f.m, f.n)) {
-    const int sides = whole_sides(f.m, f.n);
+  if (tab && !fast && whole_sides(kWholeGram, f.m, f.n)) {
+    const int sides = whole_sides(kWholeGram, f.m, f.n);
     const int64_t n = problems * gram_plan(f.m, f.n, sides, 1, f.cus).G, rounds = (n + f.cus - 1) / f.cus;
     if (n >= 2 * f.cus || 100 * n >= 85 * rounds * f.cus) whole = fast = sides;
   }

@@ -15,7 +15,8 @@ from paper_2607_27042_amd import binding, workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n", [(1, 64), (63, 64), (64, 65), (96, 1), (1024, 31), (1025, 33), (1152, 127), (1600, 66)])
+@pytest.mark.parametrize("m,n", [(1, 64), (63, 64), (64, 65), (96, 1), (1024, 31), (1025, 33), (1152, 127), (1600, 66),
+                                 (1024, 1088)])
 @pytest.mark.parametrize("reverse", [False, True])
 def test_routes_match_oracle(m, n, reverse):
     p = wl.random_problem(m, n, 41, "f64", "general")
@@ -53,9 +54,10 @@ def test_batch_routes_same_bits(m, n, count):
 
 # tiles of 64 x 64 and of 128 x 128 fill 256 compute units from 5/4 and from 0.85 per
 # unit (one or two rounds) or two per unit on: Grams on 64 x 64 tiles, ragged and
-# whole; on whole 128 x 128 tiles, one side or both, a round and more
+# whole; on whole 128 x 128 tiles, one side or both, a round and more; beside a larger
+# side
 @pytest.mark.parametrize("m,n,count", [(512, 384, 6), (700, 321, 4), (130, 70, 60), (1024, 896, 4), (640, 512, 9),
-                                       (768, 200, 26), (64, 1024, 16)])
+                                       (768, 200, 26), (64, 1024, 16), (1024, 1100, 3), (1250, 896, 3)])
 @pytest.mark.parametrize("kind", ["upper", "lower", "blocks"])
 @pytest.mark.parametrize("dtype,reverse", [(torch.float32, False), (torch.float32, True), (torch.float64, True)])
 def test_batch_gram_routes_same_bits(m, n, count, kind, dtype, reverse):
