@@ -934,8 +934,25 @@ struct BatchLaunch {
   int off[BATCH_MAX + 1];
 };
 
-__device__ __forceinline__ StageArgs batch_args(const BatchProb& q, int* flags) {
-  StageArgs a = *q.base;
+// Tables that no work group of the launch writes, through the scalar cache: as
+// ordinary loads, which the kernel's stores might alias, they would put the problem's
+// arguments into 50 vector registers of every lane, and two would spill.
+template <typename S>
+__device__ __forceinline__ S scalar_load(const S* p) {
+  typedef const __attribute__((address_space(4))) uint64_t* words;
+  static_assert(sizeof(S) % sizeof(uint64_t) == 0, "loaded in 8-byte words");
+  const words q = (words)(uintptr_t)p;
+  uint64_t w[sizeof(S) / sizeof(uint64_t)];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(S) / sizeof(uint64_t); ++i) w[i] = q[i];
+  S s;
+  __builtin_memcpy(&s, w, sizeof(S));
+  return s;
+}
+
+__device__ __forceinline__ StageArgs batch_args(const BatchProb* prob, int* flags) {
+  const BatchProb q = scalar_load(prob);
+  StageArgs a = scalar_load(q.base);
   a.X = q.X;
   a.ldx = q.ldx;
   a.Z = q.Z;
@@ -964,10 +981,10 @@ __global__ __launch_bounds__(ST) void k_stage_batch(BatchLaunch bl) {
     if (bl.off[mid] <= b) lo = mid;
     else hi = mid - 1;
   }
-  StageArgs a = batch_args(bl.desc[lo], bl.flags);
+  StageArgs a = batch_args(bl.desc + lo, bl.flags);
   a.obj = bl.obj ? bl.obj + lo : nullptr;
   const int k = bl.stage, lb = b - bl.off[lo];
-  const int4 st = a.stab[k];
+  const int4 st = scalar_load(a.stab + k);
   a.stage = k;
   int ihi;
   stage_rows(a.MT, a.NT, k, a.ilo, ihi);
