@@ -149,12 +149,12 @@ def _export(f):
     return [t.cpu().numpy() for t in (L, U, lamL, lamU)]
 
 
-# repeated shapes go through the common launches: the 64-wide Gram path
-# (130 x 200), the 128-wide one (384 x 128), Gram tiles split between work
-# groups (640 x 384), several panel groups with the far update on the second
-# stream (600 x 520), single tiles; a lone shape takes the single-problem path
+# repeated shapes go through the common launches: one panel group (130 x 200),
+# several with the far update on the second stream (640 x 384, 600 x 520), single
+# tiles, Gram tiles of 128 x 128 split between work groups (1217 x 1152); a lone
+# shape takes the single-problem path
 BATCH_SHAPES = [(130, 200), (384, 128), (130, 200), (640, 384), (600, 520), (64, 64), (384, 128),
-                (5, 7), (640, 384), (130, 200), (600, 520), (64, 64), (1, 1), (1, 1)]
+                (5, 7), (640, 384), (130, 200), (600, 520), (64, 64), (1, 1), (1, 1), (1217, 1152), (1217, 1152)]
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])

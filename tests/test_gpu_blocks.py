@@ -1,6 +1,7 @@
 """The tile sweep works on 4 x 4 blocks in bands of 16 rows; here are the
 shapes where a block, a band or a tile ends, with factors far from the
-identity, in both orders and types. The trajectory is replayed by the oracle
+identity, in both orders and types, and those where the width of the delivery
+batches changes. The trajectory is replayed by the oracle
 under the library's own factors: Z must match entry by entry, and Y, an fp64
 sum of at most m + n products, must agree to 1e-9 (2e-6 of the largest value
 where it leaves as fp32)."""
@@ -31,3 +32,22 @@ def test_block_edges(m, n, dtype, reverse):
     assert np.abs(Y - Yo).max() <= tol
     X, A, B = p.widened()
     pr.assert_objective(p, res["obj"], oracle.objective(X, flip(Zo), A, B))
+
+
+def test_delivery_widths_same_bits(monkeypatch):
+    """The width decides which sources share a product, not the order of the sums."""
+    p = wl.random_problem(1000, 700, 32, "f64", "general")
+    ref = pr.gpu_run(p)
+    for width in (1, 2, 3, 4, 5, 7):
+        monkeypatch.setenv("GPTQ2D_BATCH", str(width))
+        res = pr.gpu_run(p)
+        assert np.array_equal(res["Z"], ref["Z"]) and np.array_equal(res["Y"], ref["Y"]), width
+
+
+# 640 and 1280 products of 64^3 a launch (40 x 32, 64 x 40 tiles) are the last with
+# widths 2 and 3; beyond, 4 up to 64 tiles a side and 5 above
+@pytest.mark.parametrize("m,n", [(2560, 2048), (2624, 2048), (4096, 2560), (4096, 2624), (4160, 2560)])
+def test_delivery_width_edges(m, n):
+    p = wl.random_problem(m, n, 33, "f64", "general")
+    res = pr.gpu_run(p)
+    pr.assert_trajectory(p, res)

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,n", [(1, 64), (63, 64), (64, 65), (96, 1), (1024, 31), (1025, 33), (1152, 127), (1600, 66),
-                                 (1024, 1088)])
+                                 (1024, 1088), (66, 1217)])
 @pytest.mark.parametrize("reverse", [False, True])
 def test_routes_match_oracle(m, n, reverse):
     p = wl.random_problem(m, n, 41, "f64", "general")
@@ -93,6 +93,26 @@ def test_small_side_beside_a_large_one():
     right = binding.Factors.from_bases(pr.to_dev(q.A), pr.to_dev(q.B)).export()
     for got, ref in ((both[0], left[0]), (both[1], right[1]), (both[2], left[2]), (both[3], right[3])):
         assert (got - ref).abs().max() <= 1e-12 * ref.abs().max()
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("m,n,count", [(512, 384, 1), (512, 384, 6), (1024, 896, 4), (1152, 100, 1), (1152, 100, 2)])
+def test_nonfinite_entry_beside_zero_blocks(value, m, n, count):
+    """The larger Gram tiles skip products with a block of zeros; a NaN or an
+    infinity in the other block still reaches its own column's pivot."""
+    eye = [torch.eye(d, device="cuda", dtype=torch.float64) for d in (m, n)]
+    fs = [binding.Factors(m, n) for _ in range(count)]
+    As, Bs = [eye[0].clone() for _ in range(count)], [eye[1].clone() for _ in range(count)]
+    As[-1][3, m - 2] = value
+    if count == 1:
+        fs[0].compute(As[0], Bs[0])
+    else:
+        binding.factor_batched(fs, As, Bs, check=False)
+    with pytest.raises(binding.Gptq2dError) as e:
+        binding.gptq2d_factor_check(fs[-1].handle)
+    assert e.value.status == -2  # GPTQ2D_ERR_SINGULAR
+    for f in fs[:-1]:
+        binding.gptq2d_factor_check(f.handle)
 
 
 @pytest.mark.parametrize("side", ["A", "B"])
