@@ -87,24 +87,33 @@ def copy_calibration(mib: int):
     del src, dst
 
 
-def gram_flop(M, side: int, reverse: bool) -> tuple:
-    """Flops of the Gram of one side as the library forms it (lower 128 x 128
-    tiles, whole diagonal tiles), dense and on the envelope of its panel (the product of two 128-row blocks runs over the
-    64-column blocks where both hold a nonzero entry: the rest are exact
-    zeros). The panel S has S[p][k] = A[k][d-1-p] (side 0) or B[d-1-p][k]
-    (side 1), without the reversal in reverse order. Sides whose dimension is
-    not a multiple of 128 are formed densely."""
+def gram_flop(M, side: int, reverse: bool, other: int) -> tuple:
+    """Flops of the Gram of one side as the library forms it for one problem
+    whose other side has `other` columns: (dense, on the envelope).
+
+    Sides of up to 1024 columns are formed densely, on the lower 32 x 32 tiles
+    over the side padded to whole 64 x 64 blocks (one block per side: the whole
+    block). Larger ones, and sides of whole 128 x 128 tiles over 896 beside a
+    larger one, are formed on the lower 128 x 128 tiles (whole diagonal tiles)
+    of their panel padded with zeros, each over the 64-column blocks where both
+    of its 128-row blocks hold a nonzero entry: the rest are exact zeros. The
+    panel S has S[p][k] = A[k][d-1-p] (side 0) or B[d-1-p][k] (side 1), without
+    the reversal in reverse order."""
     import numpy as np
     d = M.shape[0]
-    dense = float(d) ** 3  # the lower half of d^3 multiply-adds
-    if d % 128:
+    nk = -(-d // 64)
+    if not (d > 1024 or (d > 896 and d % 128 == 0 and other > 1024)):
+        tiles = 4 if max(d, other) <= 64 else nk * (2 * nk + 1)
+        dense = tiles * 2.0 * 32 * 32 * 64 * nk
         return dense, dense
     if side == 0:
         S = M.T if reverse else M[:, ::-1].T
     else:
         S = M if reverse else M[::-1, :]
-    nb, nk = d // 128, d // 64
-    nz = (S != 0).reshape(nb, 128, nk, 64).any(axis=(1, 3))
+    nb = -(-nk // 2)
+    nz = np.zeros((128 * nb, 64 * nk), dtype=bool)
+    nz[:d, :d] = S != 0
+    nz = nz.reshape(nb, 128, nk, 64).any(axis=(1, 3))
     has = nz.any(axis=1)
     lo = np.where(has, nz.argmax(axis=1), nk)
     hi = np.where(has, nk - nz[:, ::-1].argmax(axis=1), 0)
@@ -457,8 +466,8 @@ def main():
     factor_flop_dense = (5.0 / 3.0) * (m ** 3 + n ** 3)
     # the Gram as formed on the envelope of these bases: the Cholesky and the
     # triangular inverse (d^3 / 3 each) plus the Gram's required products
-    g0 = gram_flop(prob.A, 0, args.order == "reverse")
-    g1 = gram_flop(prob.B, 1, args.order == "reverse")
+    g0 = gram_flop(prob.A, 0, args.order == "reverse", n)
+    g1 = gram_flop(prob.B, 1, args.order == "reverse", m)
     factor_flop = (2.0 / 3.0) * (m ** 3 + n ** 3) + g0[1] + g1[1]
     per_launch = sweep_flop / stages
     assert stage_launches == stages * args.steps, (stage_launches, stages, args.steps)
