@@ -165,8 +165,11 @@ gptq2d_status gptq2d_factors_create(int m, int n, gptq2d_factors_t* out) {
     // narrow ones win. Rounds in us at widths 2 / 3 / 4 / 5: 1000 x 700 (88 per
     // launch) 718 / 750 / 822 / 956, 2048 x 2048 (512) 1853 / 1975 / 2178 / 2709,
     // 3000 x 2000 (752) 2570 / 2531 / 2787 / 3529, 1024 x 8192 (1024) 5082 / 4808 /
-    // 5278 / 6786, 4096 x 4096 (2048) 5754 / 6083 / 5339 / 6299; five from about 128
-    // tiles a side on
+    // 5278 / 6786, 4096 x 4096 (2048) 5754 / 6083 / 5339 / 6299. Five with more than 64
+    // tiles on a side, for large problems: at widths 3 / 4 / 5 in ms 5120 x 5120 9.44 /
+    // 9.86 / 8.76, 6144 x 6144 14.7 / 14.6 / 13.2. That line is too low for problems
+    // little or less than that: 4160 x 4160 6.00 / 6.33 / 6.29, 4160 x 2560 3.59 / 4.14 /
+    // 4.89, 2048 x 8192 7.12 / 7.91 / 8.00
     const int per_launch = f->MT * f->NT / 2;
     // A batch fills the device, so there the fewer passes count at any size (64
     // problems of 512 x 384: 1.91 ms at four, 1.99 at two). The sums come in the

@@ -1911,9 +1911,9 @@ static gptq2d_status factor_impl(Factors& f, const FacProb* tab, int count, gptq
   const int GROUP = !tab && nbmax <= kOneGroup ? nbmax : nbmax > 96 ? 8 : 4;
   // A right-looking problem subtracts one panel's product after another from Q (with
   // one group all of them); a batch, which takes more of them per pass, then
-  // subtracts each by itself, too: the same bits. (Started from the old values instead, every term would
-  // round at Q's magnitude: factors of a triangular 512 basis 5.1e-15 from long
-  // double, now 3.2e-15, the times level.)
+  // subtracts each by itself, too: the same bits. (Started from Q's values instead,
+  // every term would round at their magnitude: factors of a triangular 512 basis
+  // 5.1e-15 from long double, now 3.2e-15, the times level.)
   const int each = nbmax <= kOneGroup, each_in = nbmax <= kRightLooking;
   auto update = [&](const UpdRange& r, hipStream_t st) {
     go(h_upd_count(nb0, r) + h_upd_count(nb1, r), st, [&](auto bat, dim3 g, BatchCtx bc, hipStream_t q) {

@@ -73,7 +73,7 @@ extern "C" gptq2d_status gptq2d_round_noalloc(gptq2d_factors_t f, gptq2d_dtype d
   st = scratch_address(f->device, &base);
   if (st != GPTQ2D_OK) return st;
   // the sweep's buffers in this device's scratch; the error word is the
-  // caller's (the sweep clears it with a kernel before its first stage)
+  // caller's (the sweep's first launch sets it)
   Workspace ws = workspace_carve(*f, base);
   ws.flags = status_word;
   return launch_round(*f, dt, X, ldx, Z, ldz, Y, ldy, objective, ws, (hipStream_t)stream,

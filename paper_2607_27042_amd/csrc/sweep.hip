@@ -96,7 +96,9 @@ constexpr int TCN = TB * TC + PAD;
 //   Us: U_JJ, unit upper. Block row J' is read up to block column J' + 15: past
 //     a row's end follow its 12 zeros and the lower triangle of the next rows.
 //     What is read in front of Us (Ct) or behind it (Et) belongs to blocks
-//     outside the tile and meets a zero; like everything here it is finite.
+//     outside the tile and meets a zero; like everything here it is finite if X
+//     is. (A NaN or an infinity in X spreads to other entries of its tile and of
+//     later ones; it is reported, and Z and Y are then undefined.)
 // Before the sweep the bytes of Et and Xs stage the two neighbour products.
 struct SweepSmem {
   double Ct[TCN];
@@ -1171,7 +1173,11 @@ void schedule_tasks(int MT, int NTt, int g, std::vector<int4>& all, std::vector<
 // beside the sweeps; the others only when a sweep is done, so they start
 // loaded with its duration (and stay empty when the work fits beside the
 // sweeps).
-// (least-squares fit of measured bin durations at 4096 and 8192)
+// (The costs of the products are a least-squares fit of bin durations at 4096 and 8192
+// that was made with four waves a delivery; with eight a chunk onto 2 x 2 tiles has
+// about 3.4 of matrix work. The sweep's was lowered from 45 with the 4 x 4 blocks,
+// whose tiles take about 23. What they are for is the ratio between bins: the
+// launches they add up to are within 10 % of the measured rounds.)
 constexpr double kSweepCost = 35.0;   // one tile sweep
 constexpr double kChunk4 = 5.1;       // 32-deep chunk onto 2 x 2 tiles
 constexpr double kChunk2 = 2.4;       // onto 2 x 1 or 1 x 2 tiles
