@@ -511,7 +511,8 @@ __global__ __launch_bounds__(NT) void k_gram_prep(FacArgs f0, const T* A0, int64
 // (i0, i1 select the part i0 <= i < i1 of the loads)
 // (a last, half row block is followed by 64 rows of the buffer that nobody has
 // written; what comes of them is not stored)
-__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int c, GramChunk& g, int w, int l, int i0 = 0, int i1 = 8) {
+__device__ __forceinline__ void gram_issue(const double* Sp, const double* Sq, int64_t ld, int c, GramChunk& g, int w,
+                                           int l, int i0 = 0, int i1 = 8) {
   typedef __attribute__((address_space(3))) void lds_v;
   const int ar = l >> 4, ap = (l & 15) ^ ar;
   const int64_t k0 = (int64_t)c * GQ + 2 * ap;
